@@ -244,8 +244,11 @@ int himuon_ns_tiled_noalloc(int64_t n_mats,
  *                     problem table, the iterate buffers of one chunk and
  *                     the GEMM library's scratch (64 MiB).
  * chunk_budget_bytes  bound on a chunk's iterate buffers (2 m n + 2 m^2
- *                     operand elements per problem); 0 = every problem of a
- *                     shape in one chunk (at most 65535).
+ *                     operand elements per problem, m and n rounded up to
+ *                     multiples of 64 where the library's own products
+ *                     serve it; one unrounded problem is always enough);
+ *                     0 = every problem of a shape in one chunk (at most
+ *                     65535).
  *
  * The first call on a device creates the GEMM library's handle there (its
  * own host and device resources, once per process); calls after that

@@ -35,6 +35,7 @@ SOURCES = [
     ("ns_tiled_noalloc.hip", []),
     ("ns_rect.hip", []),
     ("ns_gemm_kernels.hip", []),
+    ("ns_block_gemm.hip", []),
     ("optim_kernels.hip", []),
     ("himuon_api.cpp", []),
     ("ns_gemm_path.cpp", []),

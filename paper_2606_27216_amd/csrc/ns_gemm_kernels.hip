@@ -198,8 +198,16 @@ __device__ __forceinline__ void store_x8(void* xv, int64_t idx, int n, bool vec,
     }
 }
 
+// Element (i, j) of an m x n iterate: row-major, or in panels of 32 columns
+// (the block products' layout, ns_block_gemm.hip). Chunks of eight elements
+// stay whole in both.
+__device__ __forceinline__ int64_t iterate_index(int i, int j, int m, int n, int panels)
+{
+    return panels ? ((int64_t)(j >> 5) * m + i) * 32 + (j & 31) : (int64_t)i * n + j;
+}
+
 template <GemmStore ST, GemmOperand OP, bool OPT>
-__global__ void __launch_bounds__(kThreads) gemm_gather(const GemmProb* probs, int m, int n, int nparts,
+__global__ void __launch_bounds__(kThreads) gemm_gather(const GemmProb* probs, int m, int n, int panels, int nparts,
                                                         const double* partial, void* xv, const OptArgs o)
 {
     typedef typename OpType<OP>::T OT;
@@ -227,7 +235,7 @@ __global__ void __launch_bounds__(kThreads) gemm_gather(const GemmProb* probs, i
         }
 #pragma unroll
         for (int e = 0; e < 8; ++e) v[e] = (float)((double)v[e] * s);
-        store_x8<OP>(x, (int64_t)i * n + j, min(8, n - j), n % 8 == 0, v);
+        store_x8<OP>(x, iterate_index(i, j, m, n, panels), min(8, n - j), n % 8 == 0, v);
     } else {
         // iterate (i, j) = block (j, i): block rows j0.., columns i0.. through LDS
         __shared__ float t[32][33];
@@ -246,14 +254,14 @@ __global__ void __launch_bounds__(kThreads) gemm_gather(const GemmProb* probs, i
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
                 const int i = i0 + ty + 8 * k, j = jh + tx;
-                if (i < m && j < n) x[(int64_t)i * n + j] = (OT)t[tx][ty + 8 * k];
+                if (i < m && j < n) x[iterate_index(i, j, m, n, panels)] = (OT)t[tx][ty + 8 * k];
             }
         }
     }
 }
 
 template <GemmStore ST, GemmOperand OP, bool OPT>
-__global__ void __launch_bounds__(kThreads) gemm_scatter(const GemmProb* probs, int m, int n, float inv_scale,
+__global__ void __launch_bounds__(kThreads) gemm_scatter(const GemmProb* probs, int m, int n, int panels, float inv_scale,
                                                          const void* xv, const OptArgs o)
 {
     typedef typename OpType<OP>::T OT;
@@ -267,7 +275,7 @@ __global__ void __launch_bounds__(kThreads) gemm_scatter(const GemmProb* probs, 
         if (i >= P.h || j >= P.w) return;
         const int nv = min(8, P.w - j);
         float u[8];
-        load_x8<OP>(x, (int64_t)i * n + j, nv, n % 8 == 0 && nv == 8, u);
+        load_x8<OP>(x, iterate_index(i, j, m, n, panels), nv, n % 8 == 0 && nv == 8, u);
 #pragma unroll
         for (int e = 0; e < 8; ++e) u[e] *= inv_scale;
         const bool vec = (P.vec & GEMM_VEC_OUT) && nv == 8;
@@ -291,7 +299,7 @@ __global__ void __launch_bounds__(kThreads) gemm_scatter(const GemmProb* probs, 
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
                 const int i = i0 + ty + 8 * k, j = jh + tx;
-                t[ty + 8 * k][tx] = (i < m && j < n) ? (float)x[(int64_t)i * n + j] * inv_scale : 0.f;
+                t[ty + 8 * k][tx] = (i < m && j < n) ? (float)x[iterate_index(i, j, m, n, panels)] * inv_scale : 0.f;
             }
             __syncthreads();
             // block (r, c) = iterate (c, r): block rows jh.., columns i0..
@@ -330,7 +338,7 @@ hipError_t launch_gemm_norm_partials(GemmStore st, const GemmProb* probs, int np
     return hipGetLastError();
 }
 
-hipError_t launch_gemm_gather(GemmStore st, GemmOperand op, const GemmProb* probs, int nprob, int m, int n,
+hipError_t launch_gemm_gather(GemmStore st, GemmOperand op, const GemmProb* probs, int nprob, int m, int n, int panels,
                               int nparts, const double* partial, double scale, void* x, const OptArgs* opt,
                               hipStream_t stream)
 {
@@ -344,10 +352,10 @@ hipError_t launch_gemm_gather(GemmStore st, GemmOperand op, const GemmProb* prob
 #define HM_GATHER(S, O)                                                                                              \
     do {                                                                                                             \
         if (opt)                                                                                                     \
-            hipLaunchKernelGGL((gemm_gather<S, O, true>), grid, dim3(kThreads), 0, stream, probs, m, n, nparts,      \
+            hipLaunchKernelGGL((gemm_gather<S, O, true>), grid, dim3(kThreads), 0, stream, probs, m, n, panels, nparts,      \
                                partial, x, o);                                                                       \
         else                                                                                                         \
-            hipLaunchKernelGGL((gemm_gather<S, O, false>), grid, dim3(kThreads), 0, stream, probs, m, n, nparts,     \
+            hipLaunchKernelGGL((gemm_gather<S, O, false>), grid, dim3(kThreads), 0, stream, probs, m, n, panels, nparts,     \
                                partial, x, o);                                                                       \
     } while (0)
     if (st == GemmStore::F32 && op == GemmOperand::F32) HM_GATHER(GemmStore::F32, GemmOperand::F32);
@@ -358,7 +366,7 @@ hipError_t launch_gemm_gather(GemmStore st, GemmOperand op, const GemmProb* prob
     return hipGetLastError();
 }
 
-hipError_t launch_gemm_scatter(GemmStore st, GemmOperand op, const GemmProb* probs, int nprob, int m, int n,
+hipError_t launch_gemm_scatter(GemmStore st, GemmOperand op, const GemmProb* probs, int nprob, int m, int n, int panels,
                                float inv_scale, const void* x, const OptArgs* opt, hipStream_t stream)
 {
     if (nprob <= 0) return hipSuccess;
@@ -367,10 +375,10 @@ hipError_t launch_gemm_scatter(GemmStore st, GemmOperand op, const GemmProb* pro
 #define HM_SCATTER(S, O)                                                                                             \
     do {                                                                                                             \
         if (opt)                                                                                                     \
-            hipLaunchKernelGGL((gemm_scatter<S, O, true>), grid, dim3(kThreads), 0, stream, probs, m, n, inv_scale,  \
+            hipLaunchKernelGGL((gemm_scatter<S, O, true>), grid, dim3(kThreads), 0, stream, probs, m, n, panels, inv_scale,  \
                                x, o);                                                                                \
         else                                                                                                         \
-            hipLaunchKernelGGL((gemm_scatter<S, O, false>), grid, dim3(kThreads), 0, stream, probs, m, n, inv_scale, \
+            hipLaunchKernelGGL((gemm_scatter<S, O, false>), grid, dim3(kThreads), 0, stream, probs, m, n, panels, inv_scale, \
                                x, o);                                                                                \
     } while (0)
     if (st == GemmStore::F32 && op == GemmOperand::F32) HM_SCATTER(GemmStore::F32, GemmOperand::F32);

@@ -15,8 +15,11 @@
 // every m when the scalar iterates stay below the bound checked at planning
 // (himuon_select_compute's argument, on |X|, |A| and |B|); s = 1 for fp32 and
 // bf16 operands. Accumulation is fp32 in every
-// mode. The GEMMs are hipBLASLt's (column-major: a row-major m x n iterate
-// is an n x m column-major matrix, and A and B are symmetric).
+// mode. 16-bit operands run on the block products (ns_block_gemm.hip: the upper
+// halves of A and B only, a I taken into B, iterates in panels); fp32 operands,
+// c = 0 and iterates of few rows on hipBLASLt's GEMMs (column-major: a
+// row-major m x n iterate is an n x m column-major matrix, and A and B are
+// symmetric).
 #include "ns_gemm_path.h"
 #include "himuon_internal.h"
 #include "../../include/himuon.h"
@@ -53,7 +56,9 @@ hipDataType op_type(GemmOperand op)
 // ---- shapes and chunks
 
 struct Group {
-    int m = 0, n = 0;      // iterate shape
+    int m0 = 0, n0 = 0;    // problem shape
+    int m = 0, n = 0;      // iterate shape: the problem's, or (own) rounded up to multiples of 64 with zeros
+    bool own = false;      // the products run on block_gemm instead of the library
     int nparts = 1;        // norm partials per problem
     int64_t count = 0;     // problems
     int64_t first = 0;     // index of the group's first problem in the call's table
@@ -101,8 +106,8 @@ int plan_groups(int64_t n_mats, const int64_t* rows, const int64_t* cols, int Th
         auto it = index.find(key);
         if (it == index.end()) {
             Group g;
-            g.m = (int)m;
-            g.n = (int)n;
+            g.m0 = g.m = (int)m;
+            g.n0 = g.n = (int)n;
             g.nparts = group_nparts((int)n);
             it = index.emplace(key, groups.size()).first;
             groups.push_back(g);
@@ -120,6 +125,26 @@ int plan_groups(int64_t n_mats, const int64_t* rows, const int64_t* cols, int Th
     return HIMUON_OK;
 }
 
+// Takes the groups that the block products (ns_block_gemm.hip) serve: 16-bit
+// operands, c != 0 (their B' = alpha (A A + (beta / alpha) A) + a I divides by
+// alpha), row offsets inside 32 bits, and iterates that at most double when
+// rounded up to multiples of 64. Measured against the tuned library products
+// (us a call, K = 5, 2048 x 2048 cut into Th x Tw): 64 x 64 186 / 261, 96 x 96
+// 186 / 290, 128 x 128 130 / 204, 192 x 192 144 / 394, 256 x 256 128 / 263,
+// 128 x 512 93 / 197; whole 100 x 3000 128 / 205, 200 x 200 77 / 478. Below 64
+// rows most of a tile would be padding, so those stay with the library.
+void choose_route(std::vector<Group>& groups, GemmOperand op, float b, float c)
+{
+    for (Group& g : groups) {
+        const int64_t m = ceil_div(g.m0, 64) * 64, n = ceil_div(g.n0, 64) * 64;
+        g.own = op != GemmOperand::F32 && c != 0.f && fabs((double)b / (double)c) < 1e20 && n <= (1 << 22) &&
+                m * (m + n) <= 2 * (int64_t)g.m0 * ((int64_t)g.m0 + g.n0);
+        if (!g.own) continue;
+        g.m = (int)m;
+        g.n = (int)n;
+    }
+}
+
 // Chunk capacity per group under `budget` (0: everything in one chunk, up
 // to the launch limit) and the workspace bytes the call needs.
 int plan_chunks(std::vector<Group>& groups, GemmOperand op, size_t budget, size_t* ws_bytes)
@@ -132,9 +157,9 @@ int plan_chunks(std::vector<Group>& groups, GemmOperand op, size_t budget, size_
         g.bytes_pp = (2 * mn + 2 * mm) * es;
         int64_t cap = g.count;
         if (budget) {
-            const int64_t fit = (int64_t)(budget / g.bytes_pp);
-            if (fit < 1) return HIMUON_ERR_WORKSPACE;
-            cap = std::min<int64_t>(cap, fit);
+            // (a budget of one problem is enough, whatever its iterate is rounded up to)
+            if (budget < (2 * (size_t)g.m0 * g.n0 + 2 * (size_t)g.m0 * g.m0) * es) return HIMUON_ERR_WORKSPACE;
+            cap = std::min<int64_t>(cap, std::max<int64_t>(1, (int64_t)(budget / g.bytes_pp)));
         }
         cap = std::min<int64_t>(cap, kMaxChunkProbs);
         g.n_chunks = ceil_div(g.count, cap);
@@ -367,6 +392,7 @@ int run_gemm_path(int64_t n_mats, const void* const* in_ptrs, void* const* out_p
     GemmOperand op;
     st = resolve_operand(dtype, compute, K, a, b, c, m_max, &op);
     if (st != HIMUON_OK) return st;
+    choose_route(groups, op, b, c);
     size_t need = 0;
     st = plan_chunks(groups, op, chunk_budget_bytes, &need);
     if (st != HIMUON_OK) return st;
@@ -431,6 +457,7 @@ int run_gemm_path(int64_t n_mats, const void* const* in_ptrs, void* const* out_p
     hipblasLtHandle_t lt = nullptr;
     int status = HIMUON_OK;
     for (const Group& g : groups) {
+        if (g.own) continue;
         const int64_t small = g.count / g.n_chunks, big = ceil_div(g.count, g.n_chunks);
         Plan* pl = nullptr;
         status = get_plan(dev, g.m, g.n, (int)big, op, &lt, &pl);
@@ -460,7 +487,7 @@ int run_gemm_path(int64_t n_mats, const void* const* in_ptrs, void* const* out_p
         void* X[2] = {bufs, bufs + xb};
         void* A = bufs + 2 * xb;
         void* B = bufs + 2 * xb + ab;
-        const double s = iterate_scale(op, g.m);
+        const double s = iterate_scale(op, g.m0);
         const float alpha2 = (float)((double)c / (s * s * s * s)), beta2 = (float)((double)b / (s * s));
         for (int64_t ci = 0; ci < g.n_chunks && status == HIMUON_OK; ++ci) {
             const int64_t p0 = (int64_t)(((__int128)ci * g.count) / g.n_chunks);
@@ -468,10 +495,10 @@ int run_gemm_path(int64_t n_mats, const void* const* in_ptrs, void* const* out_p
             const int np = (int)(p1 - p0);
             const GemmProb* tp = table + g.first + p0;
             Plan* pl = nullptr;
-            status = get_plan(dev, g.m, g.n, np, op, &lt, &pl);
+            if (!g.own) status = get_plan(dev, g.m, g.n, np, op, &lt, &pl);
             if (status != HIMUON_OK) break;
             if ((e = himuon::launch_gemm_norm_partials(sto, tp, np, g.nparts, partial, opt, hs)) != hipSuccess ||
-                (e = himuon::launch_gemm_gather(sto, op, tp, np, g.m, g.n, g.nparts, partial, s, X[0], opt, hs)) !=
+                (e = himuon::launch_gemm_gather(sto, op, tp, np, g.m, g.n, g.own, g.nparts, partial, s, X[0], opt, hs)) !=
                     hipSuccess) {
                 status = himuon::set_hip_error(e);
                 break;
@@ -480,13 +507,19 @@ int run_gemm_path(int64_t n_mats, const void* const* in_ptrs, void* const* out_p
             for (int k = 0; k < K && status == HIMUON_OK; ++k) {
                 void* x = X[cur_x];
                 void* xn = X[cur_x ^ 1];
+                if (g.own) {
+                    e = himuon::launch_block_step(op, g.m, g.n, np, alpha2, beta2, a, x, A, B, xn, hs);
+                    if (e != hipSuccess) status = himuon::set_hip_error(e);
+                    cur_x ^= 1;
+                    continue;
+                }
                 status = run_gemm(lt, pl->gram, 1.f, x, x, 0.f, A, A, lt_ws, hs);
                 if (status == HIMUON_OK) status = run_gemm(lt, pl->poly, alpha2, A, A, beta2, A, B, lt_ws, hs);
                 if (status == HIMUON_OK) status = run_gemm(lt, pl->apply, 1.f, x, B, a, x, xn, lt_ws, hs);
                 cur_x ^= 1;
             }
             if (status == HIMUON_OK &&
-                (e = himuon::launch_gemm_scatter(sto, op, tp, np, g.m, g.n, (float)(1.0 / s), X[cur_x], opt, hs)) !=
+                (e = himuon::launch_gemm_scatter(sto, op, tp, np, g.m, g.n, g.own, (float)(1.0 / s), X[cur_x], opt, hs)) !=
                     hipSuccess)
                 status = himuon::set_hip_error(e);
         }
@@ -505,6 +538,7 @@ size_t gemm_path_workspace(int64_t n_mats, const int64_t* rows, const int64_t* c
     GemmOperand op;
     if (dtype != HIMUON_F32 && dtype != HIMUON_BF16) return 0;
     if (resolve_operand(dtype, compute, K, a, b, c, m_max, &op) != HIMUON_OK) return 0;
+    choose_route(groups, op, b, c);
     size_t ws = 0;
     if (plan_chunks(groups, op, chunk_budget_bytes, &ws) != HIMUON_OK) return 0;
     return ws;
@@ -569,6 +603,7 @@ int himuon_gemm_tune_hw(int64_t n_mats, const int64_t* rows, const int64_t* cols
     GemmOperand op;
     st = resolve_operand(dtype, compute, K, a, b, c, m_max, &op);
     if (st != HIMUON_OK) return st;
+    choose_route(groups, op, b, c);
     size_t need = 0;
     st = plan_chunks(groups, op, chunk_budget_bytes, &need);
     if (st != HIMUON_OK) return st;
@@ -601,12 +636,13 @@ int himuon_gemm_tune_hw(int64_t n_mats, const int64_t* rows, const int64_t* cols
     void* const lt_ws = bufs + buf_max;
     for (const Group& g : groups) {
         if (st != HIMUON_OK) break;
+        if (g.own) continue;  // nothing to choose
         const size_t xb = align_up((size_t)g.cap * g.m * g.n * es), ab = align_up((size_t)g.cap * g.m * g.m * es);
         uint8_t* const X0 = bufs;
         uint8_t* const X1 = bufs + xb;
         uint8_t* const A = bufs + 2 * xb;
         uint8_t* const B = bufs + 2 * xb + ab;
-        const double s = iterate_scale(op, g.m);
+        const double s = iterate_scale(op, g.m0);
         const float alpha2 = (float)((double)c / (s * s * s * s)), beta2 = (float)((double)b / (s * s));
         const int64_t sizes[2] = {ceil_div(g.count, g.n_chunks), g.count / g.n_chunks};
         for (int k = 0; k < 2 && st == HIMUON_OK; ++k) {

@@ -58,14 +58,20 @@ hipError_t launch_gemm_norm_partials(GemmStore st, const GemmProb* probs, int np
 
 // X0 = scale * B / ||B||_F (zero when the block is zero) as the m x n
 // row-major iterate of each problem, stride m * n elements.
-hipError_t launch_gemm_gather(GemmStore st, GemmOperand op, const GemmProb* probs, int nprob, int m, int n,
+hipError_t launch_gemm_gather(GemmStore st, GemmOperand op, const GemmProb* probs, int nprob, int m, int n, int panels,
                               int nparts, const double* partial, double scale, void* x, const OptArgs* opt,
                               hipStream_t stream);
 
 // Output block = inv_scale * (the block's part of the iterate), rounded to
 // the storage type (nearest even for bf16).
-hipError_t launch_gemm_scatter(GemmStore st, GemmOperand op, const GemmProb* probs, int nprob, int m, int n,
+hipError_t launch_gemm_scatter(GemmStore st, GemmOperand op, const GemmProb* probs, int nprob, int m, int n, int panels,
                                float inv_scale, const void* x, const OptArgs* opt, hipStream_t stream);
+
+// One Newton-Schulz step on `batch` m x n iterates (16-bit operands; m, n
+// multiples of 64) through the block products: A = X X^T, B = alpha A A +
+// beta A + diag I, x_out = B X. alpha != 0.
+hipError_t launch_block_step(GemmOperand op, int m, int n, int batch, float alpha, float beta, float diag,
+                             const void* x, void* A, void* B, void* x_out, hipStream_t stream);
 
 // Core of himuon_ns_gemm(_hw) and of the optimizer step on the GEMM path
 // (`opt` null: Phi of `in` into `out`), with Th x Tw tiles (0 x 0: whole
