@@ -33,7 +33,7 @@
 // LDS reads over the products, with waits that the compiler knows of, took GRAM
 // at 2048 x 6144 from 93 to 84 and APPLY from 163 to 130; a ring of five or of
 // two 64-deep slices, row-major iterates or 256-tiles changed nothing by 3%.
-#include "ns_gemm_path.h"
+#include "elementwise8.h"
 #include "ns_device.h"
 
 #include <type_traits>
@@ -56,7 +56,15 @@ struct BlkArgs {
     int32_t total;       // tiles of the launch
     float alpha, ratio;  // POLY: B' = alpha (A A + ratio A) + diag I
     float diag;
+    // APPLY as the last step: results go to the caller's matrices (scaled by
+    // inv_scale, rounded to bf16) or, with the optimizer step, into its weights
+    const GemmProb* probs;
+    float inv_scale;
+    OptArgs opt;
 };
+
+// where APPLY's results go: the next iterate, the output matrices, the weights
+enum class Dest : int { ITERATE, OUT, WEIGHTS };
 
 HM_DEV u32x2 tr_read(const uint8_t* ptr)
 {
@@ -93,7 +101,7 @@ template <int N> HM_DEV void dma_wait_barrier()
 
 enum class Product : int { GRAM, POLY, APPLY };
 
-template <Product P, Operand OP, int BM, int BN, int WGM, int WGN, int NS, int MINW>
+template <Product P, Dest D, Operand OP, int BM, int BN, int WGM, int WGN, int NS, int MINW>
 __global__ void __launch_bounds__(64 * WGM * WGN, MINW) block_gemm(const BlkArgs p)
 {
     constexpr int W = WGM * WGN;            // waves
@@ -330,6 +338,91 @@ __global__ void __launch_bounds__(64 * WGM * WGN, MINW) block_gemm(const BlkArgs
                           pack2<OP>(acc[i][j][4 * g + 2], acc[i][j][4 * g + 3])};
             }
         }
+    // the lane's eight rows ib + 8 (lane / 16) .. of column jb + lane % 16
+    auto transposed8 = [&](int jb, int ib) -> u32x4 {
+        u32x2 h[2];
+#pragma unroll
+        for (int x = 0; x < 2; ++x) {
+            const int row = ib + 8 * g16 + 4 * x + ((lane & 15) >> 2);
+            const int c8 = jb / 4 + (lane & 3);
+            h[x] = tr_read(lds + row * (BN * 2) + 16 * ((c8 >> 1) ^ (row & 7)) + 8 * (c8 & 1));
+        }
+        return u32x4{h[0][0], h[0][1], h[1][0], h[1][1]};
+    };
+    if constexpr (D != Dest::ITERATE) {
+        // Eight consecutive elements of a row of the problem's block at a time,
+        // inside the block only. The values are those that the next iterate would
+        // hold, so the result does not depend on who scatters it. The weights are
+        // asked for before the tile is exchanged. On 128 problems of 512 x 512 the
+        // launch takes 89 us (49 into the iterate, and 34 for a scatter pass); on
+        // three of 2048 x 6144 174 (138 and 71).
+        const GemmProb Q = p.probs[prob];  // (a copy: through a reference every store reloads its fields)
+        constexpr int E = BM * BN / 8 / (64 * W);  // chunks per thread
+        constexpr int CPR = BN / 8;
+        const bool trans = Q.trans != 0;
+        auto place = [&](int e, int& r, int& c) {
+            if (!trans) {
+                const int x = (int)threadIdx.x + 64 * W * e;
+                r = i0 + x / CPR;
+                c = j0 + 8 * (x % CPR);
+            } else {
+                const int u = wave + W * e;
+                r = j0 + 16 * (u / (BM / 32)) + (lane & 15);
+                c = i0 + 32 * (u % (BM / 32)) + 8 * g16;
+            }
+        };
+        auto whole = [&](int r, int c) { return r < Q.h && c + 8 <= Q.w && (Q.vec & GEMM_VEC_OUT) != 0; };
+        u32x4 old[D == Dest::WEIGHTS ? E : 1];
+        if constexpr (D == Dest::WEIGHTS) {
+#pragma unroll
+            for (int e = 0; e < E; ++e) {
+                int r, c;
+                place(e, r, c);
+                old[e] = u32x4{};
+                if (whole(r, c))
+                    old[e] = *(const gbl_u32x4*)(static_cast<const uint16_t*>(Q.out) + (Q.row0 + r) * Q.ld_out + Q.col0 + c);
+            }
+        }
+        __syncthreads();
+        const float step = D == Dest::WEIGHTS ? p.opt.lr * Q.tau : 0.f;
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            int r, c;
+            place(e, r, c);
+            u32x4 w;
+            if (!trans) {
+                const int row = r - i0, ch = (c - j0) / 8;
+                w = *reinterpret_cast<const u32x4*>(lds + row * (BN * 2) + 16 * (ch ^ (row & 7)));
+            } else {
+                w = transposed8(r - j0 - (lane & 15), c - i0 - 8 * g16);
+            }
+            if (r >= Q.h || c >= Q.w) continue;
+            float u[8];
+#pragma unroll
+            for (int x = 0; x < 8; ++x) {
+                const uint16_t h = (uint16_t)(w[x >> 1] >> (16 * (x & 1)));
+                if constexpr (OP == Operand::F16) u[x] = (float)__builtin_bit_cast(_Float16, h) * p.inv_scale;
+                else u[x] = __uint_as_float((uint32_t)h << 16) * p.inv_scale;
+            }
+            const bool vec = whole(r, c);
+            const int nv = min(8, Q.w - c);
+            const int64_t idx = (Q.row0 + r) * Q.ld_out + Q.col0 + c;
+            if constexpr (D == Dest::WEIGHTS) {
+                float v[8];
+                if (vec) {
+#pragma unroll
+                    for (int x = 0; x < 8; ++x)
+                        v[x] = __uint_as_float((x & 1) ? (old[e][x >> 1] & 0xffff0000u) : (old[e][x >> 1] << 16));
+                } else {
+                    load8<GemmStore::BF16>(Q.out, idx, nv, false, v);
+                }
+#pragma unroll
+                for (int x = 0; x < 8; ++x) u[x] = p.opt.decay * v[x] - step * u[x];
+            }
+            store8<GemmStore::BF16>(Q.out, idx, nv, vec, u);
+        }
+        return;
+    }
     __syncthreads();
     const int ncols = SYM ? p.m : p.n;
     uint16_t* const out = p.out + prob * p.so;
@@ -351,22 +444,15 @@ __global__ void __launch_bounds__(64 * WGM * WGN, MINW) block_gemm(const BlkArgs
         for (int u = wave; u < UNITS; u += W) {
             const int jb = 16 * (u / (BM / 32)), ib = 32 * (u % (BM / 32));
             if (ti == tj && jb / 32 <= ib / 32) continue;
-            u32x2 h[2];
-#pragma unroll
-            for (int x = 0; x < 2; ++x) {
-                const int row = ib + 8 * g16 + 4 * x + ((lane & 15) >> 2);
-                const int c8 = jb / 4 + (lane & 3);
-                h[x] = tr_read(lds + row * (BN * 2) + 16 * ((c8 >> 1) ^ (row & 7)) + 8 * (c8 & 1));
-            }
+            const u32x4 v = transposed8(jb, ib);
             const int orow = j0 + jb + (lane & 15), ocol = i0 + ib + 8 * g16;
             if (orow < p.m && ocol < p.m)
-                *reinterpret_cast<u32x4*>(out + (ocol / kBK) * panel + orow * kBK + ocol % kBK) =
-                    u32x4{h[0][0], h[0][1], h[1][0], h[1][1]};
+                *reinterpret_cast<u32x4*>(out + (ocol / kBK) * panel + orow * kBK + ocol % kBK) = v;
         }
     }
 }
 
-template <Product P, Operand OP, int BM, int BN, int WGM, int WGN, int NS, int MINW>
+template <Product P, Dest D, Operand OP, int BM, int BN, int WGM, int WGN, int NS, int MINW>
 hipError_t launch_cfg(BlkArgs p, int batch, hipStream_t stream)
 {
     p.ti = (p.m + BM - 1) / BM;
@@ -375,7 +461,7 @@ hipError_t launch_cfg(BlkArgs p, int batch, hipStream_t stream)
     const int64_t total = (int64_t)p.tpp * batch;
     if (total <= 0 || total > INT32_MAX) return hipErrorInvalidValue;
     p.total = (int)total;
-    hipLaunchKernelGGL((block_gemm<P, OP, BM, BN, WGM, WGN, NS, MINW>), dim3((unsigned)total), dim3(64 * WGM * WGN), 0,
+    hipLaunchKernelGGL((block_gemm<P, D, OP, BM, BN, WGM, WGN, NS, MINW>), dim3((unsigned)total), dim3(64 * WGM * WGN), 0,
                        stream, p);
     return hipGetLastError();
 }
@@ -393,27 +479,28 @@ int64_t tiles_of(Product P, int m, int n, int batch, int bi, int bj)
 // at 128 tiles. 128 x 256 tiles of APPLY against 128-tiles, 256 and more of
 // them: m = 512 50 / 47, m = 2048 138 / 143 and 118 / 127, m = 4096 112 / 122:
 // they pay where k is long. 256 x 256 tiles won nowhere by more than 3%.
-template <Product P, Operand OP> hipError_t launch_product(const BlkArgs& p, int batch, hipStream_t stream)
+template <Product P, Dest D, Operand OP> hipError_t launch_product(const BlkArgs& p, int batch, hipStream_t stream)
 {
     if constexpr (P == Product::APPLY) {
         if (p.m >= 1024 && tiles_of(P, p.m, p.n, batch, 128, 256) >= 256)
-            return launch_cfg<P, OP, 128, 256, 2, 2, 3, 2>(p, batch, stream);
+            return launch_cfg<P, D, OP, 128, 256, 2, 2, 3, 2>(p, batch, stream);
     }
-    if (tiles_of(P, p.m, p.n, batch, 128, 128) >= 128) return launch_cfg<P, OP, 128, 128, 2, 2, 4, 2>(p, batch, stream);
-    return launch_cfg<P, OP, 64, 64, 2, 2, 8, 2>(p, batch, stream);
+    if (tiles_of(P, p.m, p.n, batch, 128, 128) >= 128) return launch_cfg<P, D, OP, 128, 128, 2, 2, 4, 2>(p, batch, stream);
+    return launch_cfg<P, D, OP, 64, 64, 2, 2, 8, 2>(p, batch, stream);
 }
 
-template <Product P> hipError_t launch_op(GemmOperand op, const BlkArgs& p, int batch, hipStream_t stream)
+template <Product P, Dest D = Dest::ITERATE> hipError_t launch_op(GemmOperand op, const BlkArgs& p, int batch, hipStream_t stream)
 {
-    if (op == GemmOperand::F16) return launch_product<P, Operand::F16>(p, batch, stream);
-    if (op == GemmOperand::BF16) return launch_product<P, Operand::BF16>(p, batch, stream);
+    if (op == GemmOperand::F16) return launch_product<P, D, Operand::F16>(p, batch, stream);
+    if (op == GemmOperand::BF16) return launch_product<P, D, Operand::BF16>(p, batch, stream);
     return hipErrorInvalidValue;
 }
 
 }  // namespace
 
 hipError_t launch_block_step(GemmOperand op, int m, int n, int batch, float alpha, float beta, float diag,
-                             const void* x, void* A, void* B, void* x_out, hipStream_t stream)
+                             const void* x, void* A, void* B, void* x_out, const GemmProb* probs, float inv_scale,
+                             const OptArgs* opt, hipStream_t stream)
 {
     if (m < 64 || n < 64 || m % 64 || n % 64) return hipErrorInvalidValue;
     const int64_t mn = (int64_t)m * n, mm = (int64_t)m * m;
@@ -439,7 +526,12 @@ hipError_t launch_block_step(GemmOperand op, int m, int n, int batch, float alph
     p.sx = mn;
     p.out = static_cast<uint16_t*>(x_out);
     p.so = mn;
-    return launch_op<Product::APPLY>(op, p, batch, stream);
+    if (!probs) return launch_op<Product::APPLY>(op, p, batch, stream);
+    p.probs = probs;
+    p.inv_scale = inv_scale;
+    if (!opt) return launch_op<Product::APPLY, Dest::OUT>(op, p, batch, stream);
+    p.opt = *opt;
+    return launch_op<Product::APPLY, Dest::WEIGHTS>(op, p, batch, stream);
 }
 
 }  // namespace himuon

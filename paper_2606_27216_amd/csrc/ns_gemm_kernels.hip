@@ -27,8 +27,8 @@ namespace {
 constexpr int kThreads = 256;
 // A block of the gather and scatter covers 32 rows x 64 columns of the
 // iterate: in the row-major orientation a thread moves one 8-column chunk;
-// a transposed block goes through LDS as two 32 x 32 tiles, four rows per
-// thread.
+// a transposed block goes through LDS (in the scatter as two 32 x 32 tiles,
+// four rows per thread).
 constexpr int kBlkRows = 32, kBlkCols = 64;
 
 template <GemmStore ST>
@@ -57,15 +57,6 @@ __device__ __forceinline__ float load_f32(const void* base, int64_t idx)
 __device__ __forceinline__ float lookahead(float g, float m_new, const OptArgs& o)
 {
     return o.nesterov ? g + o.beta * m_new : m_new;
-}
-
-// Element `idx` of the problem's input: the matrix itself, or (OPT) the
-// lookahead gradient from G (`in`) and the already updated momentum.
-template <GemmStore ST, bool OPT>
-__device__ __forceinline__ float input_elem(const GemmProb& P, int64_t idx, const OptArgs& o)
-{
-    if constexpr (OPT) return lookahead(load_f32<ST>(P.in, idx), load_f32<ST>(P.mom, idx), o);
-    else return load_f32<ST>(P.in, idx);
 }
 
 // Writes the result u of element `idx`: the plain output, or (OPT) the
@@ -101,10 +92,12 @@ __global__ void __launch_bounds__(kThreads) gemm_norm_partials(const GemmProb* p
     const int r1 = min(P.h, r0 + rpp);
     double acc = 0.0;
     // the part's rows x 8-column chunks, flattened: element e = (row, chunk)
-    const int cpr = (P.w + 7) / 8;
-    const int64_t n_e = (int64_t)max(r1 - r0, 0) * cpr;
-    for (int64_t e0 = threadIdx.x; e0 < n_e; e0 += kThreads) {
-        const int r = r0 + (int)(e0 / cpr), c = 8 * (int)(e0 % cpr);
+    // (32-bit: a part is about 8192 elements or one row)
+    const uint32_t cpr = (uint32_t)(P.w + 7) / 8u;
+    const uint32_t n_e = (uint32_t)max(r1 - r0, 0) * cpr;
+    for (uint32_t e0 = threadIdx.x; e0 < n_e; e0 += kThreads) {
+        const uint32_t dr = e0 / cpr;
+        const int r = r0 + (int)dr, c = 8 * (int)(e0 - dr * cpr);
         const int64_t rowoff = (P.row0 + r) * P.ld_in + P.col0;
         const int nv = min(8, P.w - c);
         const bool vec = (P.vec & GEMM_VEC_IN) && nv == 8;
@@ -134,14 +127,22 @@ __global__ void __launch_bounds__(kThreads) gemm_norm_partials(const GemmProb* p
 }
 
 // The problem's scale factor, scale / ||B||_F (0 for a zero block), written
-// over its first partial.
-__global__ void gemm_norm_finalize(int nprob, int nparts, double scale, double* partial)
+// over its first partial: one workgroup per problem, each thread over a fixed
+// set of partials, then a fixed-order tree.
+__global__ void __launch_bounds__(kThreads) gemm_norm_finalize(int nparts, double scale, double* partial)
 {
-    const int p = blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= nprob) return;
+    double* const part = partial + (int64_t)blockIdx.x * nparts;
     double ss = 0.0;
-    for (int j = 0; j < nparts; ++j) ss += partial[(int64_t)p * nparts + j];
-    partial[(int64_t)p * nparts] = ss > 0.0 ? scale / sqrt(ss) : 0.0;
+    for (int j = threadIdx.x; j < nparts; j += kThreads) ss += part[j];
+    __shared__ double red[kThreads];
+    red[threadIdx.x] = ss;
+    __syncthreads();
+#pragma unroll
+    for (int s = kThreads / 2; s > 0; s >>= 1) {
+        if ((int)threadIdx.x < s) red[threadIdx.x] += red[threadIdx.x + s];
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) part[0] = red[0] > 0.0 ? scale / sqrt(red[0]) : 0.0;
 }
 
 // Eight consecutive iterate elements (operand type) as fp32 / from fp32;
@@ -237,26 +238,35 @@ __global__ void __launch_bounds__(kThreads) gemm_gather(const GemmProb* probs, i
         for (int e = 0; e < 8; ++e) v[e] = (float)((double)v[e] * s);
         store_x8<OP>(x, iterate_index(i, j, m, n, panels), min(8, n - j), n % 8 == 0, v);
     } else {
-        // iterate (i, j) = block (j, i): block rows j0.., columns i0.. through LDS
-        __shared__ float t[32][33];
-        const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
-        for (int half = 0; half < 2; ++half) {
-            const int jh = j0 + 32 * half;
-            if (half) __syncthreads();
+        // iterate (i, j) = block (j, i): 64 block rows j0.. of 32 columns i0..
+        // through LDS, in chunks of eight on both sides (element by element the
+        // transposed gathers of a 6144 x 2048 step took 63 us, now 43)
+        __shared__ float t[kBlkCols][kBlkRows + 1];
+        {
+            const int r = j0 + (int)(threadIdx.x >> 2), c = i0 + 8 * (int)(threadIdx.x & 3);
+            float v[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+            if (r < P.h && c < P.w) {
+                const int nv = min(8, P.w - c);
+                const bool vec = (P.vec & GEMM_VEC_IN) && nv == 8;
+                const int64_t idx = (P.row0 + r) * P.ld_in + P.col0 + c;
+                load8<ST>(P.in, idx, nv, vec, v);
+                if constexpr (OPT) {
+                    float mm[8];
+                    load8<ST>(P.mom, idx, nv, vec, mm);
 #pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const int r = jh + ty + 8 * k, c = i0 + tx;
-                double v = 0.0;
-                if (r < P.h && c < P.w) v = (double)input_elem<ST, OPT>(P, (P.row0 + r) * P.ld_in + P.col0 + c, o) * s;
-                t[ty + 8 * k][tx] = (float)v;
+                    for (int e = 0; e < 8; ++e) v[e] = lookahead(v[e], mm[e], o);
+                }
             }
-            __syncthreads();
 #pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const int i = i0 + ty + 8 * k, j = jh + tx;
-                if (i < m && j < n) x[iterate_index(i, j, m, n, panels)] = (OT)t[tx][ty + 8 * k];
-            }
+            for (int e = 0; e < 8; ++e) t[threadIdx.x >> 2][8 * (threadIdx.x & 3) + e] = (float)((double)v[e] * s);
         }
+        __syncthreads();
+        const int i = i0 + (int)(threadIdx.x >> 3), j = j0 + 8 * (int)(threadIdx.x & 7);
+        if (i >= m || j >= n) return;
+        float v[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] = t[8 * (threadIdx.x & 7) + e][threadIdx.x >> 3];
+        store_x8<OP>(x, iterate_index(i, j, m, n, panels), min(8, n - j), n % 8 == 0, v);
     }
 }
 
@@ -343,8 +353,8 @@ hipError_t launch_gemm_gather(GemmStore st, GemmOperand op, const GemmProb* prob
                               hipStream_t stream)
 {
     if (nprob <= 0) return hipSuccess;
-    hipLaunchKernelGGL(gemm_norm_finalize, dim3((unsigned)((nprob + 255) / 256)), dim3(256), 0, stream, nprob, nparts,
-                       scale, const_cast<double*>(partial));
+    hipLaunchKernelGGL(gemm_norm_finalize, dim3((unsigned)nprob), dim3(kThreads), 0, stream, nparts, scale,
+                       const_cast<double*>(partial));
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     const dim3 grid = tile_grid(m, n, nprob);

@@ -26,6 +26,7 @@
 
 #include <hipblaslt/hipblaslt.h>
 
+#include <algorithm>
 #include <map>
 #include <math.h>
 #include <mutex>
@@ -67,7 +68,10 @@ struct Group {
     size_t bytes_pp = 0;   // iterate buffers per problem (X, X', A, B)
 };
 
-int group_nparts(int n) { return (int)std::min<int64_t>(256, std::max<int64_t>(1, ceil_div(n, 64))); }
+// Norm partials per problem: about 8192 elements each, in whole rows. A pass
+// over three 6144 x 2048 matrices by 96 parts each took 103 us; it is bound by
+// memory only once a few thousand workgroups are in flight.
+int group_nparts(int64_t m, int64_t n) { return (int)std::min<int64_t>(m, std::max<int64_t>(1, m * n / 8192)); }
 
 // Tiles are Th x Tw (square: Th = Tw = T; rectangular tiles are the
 // tile-shape study's); Th = Tw = 0 stands for T = infinity. A matrix is one
@@ -108,7 +112,7 @@ int plan_groups(int64_t n_mats, const int64_t* rows, const int64_t* cols, int Th
             Group g;
             g.m0 = g.m = (int)m;
             g.n0 = g.n = (int)n;
-            g.nparts = group_nparts((int)n);
+            g.nparts = group_nparts(m, n);
             it = index.emplace(key, groups.size()).first;
             groups.push_back(g);
             mem.emplace_back();
@@ -508,7 +512,8 @@ int run_gemm_path(int64_t n_mats, const void* const* in_ptrs, void* const* out_p
                 void* x = X[cur_x];
                 void* xn = X[cur_x ^ 1];
                 if (g.own) {
-                    e = himuon::launch_block_step(op, g.m, g.n, np, alpha2, beta2, a, x, A, B, xn, hs);
+                    e = himuon::launch_block_step(op, g.m, g.n, np, alpha2, beta2, a, x, A, B, xn,
+                                                  k == K - 1 ? tp : nullptr, (float)(1.0 / s), opt, hs);
                     if (e != hipSuccess) status = himuon::set_hip_error(e);
                     cur_x ^= 1;
                     continue;
@@ -518,7 +523,7 @@ int run_gemm_path(int64_t n_mats, const void* const* in_ptrs, void* const* out_p
                 if (status == HIMUON_OK) status = run_gemm(lt, pl->apply, 1.f, x, B, a, x, xn, lt_ws, hs);
                 cur_x ^= 1;
             }
-            if (status == HIMUON_OK &&
+            if (status == HIMUON_OK && !(g.own && K > 0) &&
                 (e = himuon::launch_gemm_scatter(sto, op, tp, np, g.m, g.n, g.own, (float)(1.0 / s), X[cur_x], opt, hs)) !=
                     hipSuccess)
                 status = himuon::set_hip_error(e);
@@ -608,6 +613,7 @@ int himuon_gemm_tune_hw(int64_t n_mats, const int64_t* rows, const int64_t* cols
     st = plan_chunks(groups, op, chunk_budget_bytes, &need);
     if (st != HIMUON_OK) return st;
     if (!workspace || workspace_bytes < need) return HIMUON_ERR_WORKSPACE;
+    if (std::all_of(groups.begin(), groups.end(), [](const Group& g) { return g.own; })) return HIMUON_OK;  // nothing to choose
 
     hipStream_t hs = static_cast<hipStream_t>(stream);
     int cur = 0, dev = 0;
@@ -636,7 +642,7 @@ int himuon_gemm_tune_hw(int64_t n_mats, const int64_t* rows, const int64_t* cols
     void* const lt_ws = bufs + buf_max;
     for (const Group& g : groups) {
         if (st != HIMUON_OK) break;
-        if (g.own) continue;  // nothing to choose
+        if (g.own) continue;
         const size_t xb = align_up((size_t)g.cap * g.m * g.n * es), ab = align_up((size_t)g.cap * g.m * g.m * es);
         uint8_t* const X0 = bufs;
         uint8_t* const X1 = bufs + xb;
