@@ -30,6 +30,11 @@
 // the end, which keeps large partial sums out of the fp32 rounding walk.
 // Operands are rounded once (fp16 or bf16, round to nearest even) or stay fp32.
 //
+// fp32 tiles of 64 and 128 evaluate only the upper blocks of the symmetric A and
+// B (40 and 36 of 48 block products; steps64, steps128 below): 24 matrices of 4M
+// entries, T = 128, K = 8 5131 -> 3893 us, T = 64, K = 5 1843 -> 1383 us: 159 and
+// 140 TFLOP/s counted as if every product were done (the fp32 MFMA peak is 157).
+//
 // LDS holds, per tile, one operand matrix of row pieces ("xr", only when a
 // tile is split over several waves; it carries X and then A) and one of
 // column pieces ("xc"), both as 16-byte-per-lane slots in lane order so
@@ -37,6 +42,7 @@
 #include "ns_device.h"
 
 #include <atomic>
+#include <type_traits>
 
 namespace himuon {
 namespace {
@@ -62,10 +68,20 @@ __global__ void __launch_bounds__(kThreads) ns_tiled_kernel(const KernelArgs arg
     constexpr int NC = OperandTraits<OP>::kChains;
     constexpr int MAT = NB * NB * S * 64;  // 16-byte slots in one operand matrix
     constexpr bool SHARED_ROWS = WT > 1;
+    // fp32 tiles of more than one block evaluate the upper blocks of the
+    // symmetric A and B only (steps64, steps128)
+    constexpr bool SYM = OP == Operand::F32 && NB > 1;
+    static_assert(!SYM || (NB == 2 && WT == 1) || (NB == 4 && WT == 4), "fp32 splits");
+    constexpr int BLK = S * 64;  // 16-byte slots of one 32x32 block
+    // block exchange: one block per 64-tile, two per wave of a 128-tile (whose
+    // 32 KB also lend the reductions of the normalisation their few bytes)
+    constexpr int EX = !SYM ? 1 : (SHARED_ROWS ? 8 * BLK : TPW * BLK);
 
     __shared__ u32x4 s_xr[SHARED_ROWS ? TPW * MAT : 1];
     __shared__ u32x4 s_xc[TPW * MAT];
-    __shared__ float s_red[2][4];
+    __shared__ u32x4 s_ex[EX];
+    __shared__ float s_own_red[SYM && SHARED_ROWS ? 1 : 8];
+    float (*const s_red)[4] = reinterpret_cast<float (*)[4]>(SYM && SHARED_ROWS ? reinterpret_cast<float*>(s_ex) : s_own_red);
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -210,6 +226,226 @@ __global__ void __launch_bounds__(kThreads) ns_tiled_kernel(const KernelArgs arg
         // ---- K Newton–Schulz steps, all on chip
         const int t4 = li & 3, quad = li >> 2;
         const int xg = quad >> 1, xh = quad & 1;  // row group of this quad in a block
+
+        // fp32 steps on the upper blocks. What bounds them is the fp32 MFMA (64
+        // cycles each) and, on the same units, the vector ALU: a v_add between two
+        // of these MFMAs adds its 4 cycles in full and a change from one to the
+        // other 13 more (measured; fp16 MFMAs hide such work, fp32 ones do not).
+        // So blocks are evaluated one at a time, each product a run of MFMAs
+        // alone, and the vector work is kept to the sums and polynomials: no
+        // copies out of accumulation registers, and transposes go through
+        // LDS by 4-byte writes instead of lane exchanges.
+#define HM_INL __attribute__((always_inline))
+        // A block's column pieces: rows 4q .. 4q + 3 of column c in the 16-byte
+        // chunk 32 q + (c ^ q), so that neither the 4-byte writes (32 rows of one
+        // column) nor the 16-byte reads (32 columns of one q) meet in a bank.
+        int twr[4], trd[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            twr[e] = 128 * (li >> 2) + 4 * ((4 * lh + e) ^ (li >> 2)) + (li & 3);
+            trd[e] = 32 * (2 * e + lh) + (li ^ (2 * e + lh));
+        }
+        auto put_t = [&](const f32x16& v, u32x4* dst) HM_INL {
+            float* const d = reinterpret_cast<float*>(dst);
+#pragma unroll
+            for (int r = 0; r < 16; ++r) d[twr[r & 3] + 32 * (r >> 2)] = v[r];
+        };
+        auto get = [&](const u32x4* src, f32x16& v) HM_INL {
+#pragma unroll
+            for (int sl = 0; sl < 4; ++sl) {
+                const u32x4 w = src[trd[sl]];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[4 * sl + e] = __uint_as_float(w[e]);
+            }
+        };
+        // acc = sum over g < NG of opa(g) x opb(g), LDS operands two groups ahead
+        auto product = [&](auto ng, auto&& opa, auto&& opb, f32x16 (&acc)[NC]) HM_INL {
+            constexpr int NG = decltype(ng)::value;
+#pragma unroll
+            for (int ch = 0; ch < NC; ++ch) acc[ch] = f32x16{};
+            u32x4 nxt[2] = {opa(0), opa(1)};
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int g = 0; g < NG; ++g) {
+                const u32x4 cur = nxt[g & 1];
+                if (g + 2 < NG) nxt[g & 1] = opa(g + 2);
+                mma<OP>(cur, opb(g), acc);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        auto sum4 = [](const f32x16 (&acc)[NC], int r) HM_INL -> float {
+            if constexpr (NC == 4) return (acc[0][r] + acc[1][r]) + (acc[2][r] + acc[3][r]);
+            else return acc[0][r];
+        };
+        auto sum = [&](const f32x16 (&acc)[NC], f32x16& v) HM_INL {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) v[r] = sum4(acc, r);
+        };
+        // b' A + c' Q, Q the sum of the chains (b' A for c = 0)
+        auto poly = [&](const f32x16& g, const f32x16 (&acc)[NC], f32x16& v) HM_INL {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) v[r] = poly2(en, g[r], sum4(acc, r));
+        };
+        auto linear = [&](const f32x16& g, f32x16& v) HM_INL {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) v[r] = fmaf(en.bh, g[r], en.bl * g[r]);
+        };
+        auto update = [&](f32x16& x, const f32x16 (&acc)[NC]) HM_INL {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) x[r] = fmaf(args.a, x[r], sum4(acc, r));
+        };
+
+        // 64-tile, one wave: block (1, 0) of A and of B is the transpose of (0, 1)
+        auto steps64 = [&](auto quintic) HM_INL {
+          if constexpr (SYM && NB == 2) {
+            constexpr bool QUINTIC = decltype(quintic)::value;  // c != 0
+            u32x4* const ex = s_ex + tslot * BLK;
+            constexpr std::integral_constant<int, 8> ng{};
+            auto op = [&](const f32x16 (&R)[2]) HM_INL { return [&](int g) HM_INL { return make_slot<OP>(R[g >> 2], g & 3); }; };
+            auto xcol = [&](int N) HM_INL { return [&, N](int g) HM_INL { return xc[((g >> 2) * 2 + N) * BLK + trd[g & 3]]; }; };
+            for (int k = 0; k < args.K; ++k) {
+                f32x16 G[2][2], B[2][2], acc[NC];
+#pragma unroll
+                for (int b = 0; b < 4; ++b) put_t(X[b >> 1][b & 1], xc + b * BLK);
+                product(ng, op(X[1]), op(X[0]), acc);
+                sum(acc, G[0][1]);
+                put_t(G[0][1], ex);
+                product(ng, op(X[0]), op(X[0]), acc);
+                sum(acc, G[0][0]);
+                get(ex, G[1][0]);
+                product(ng, op(X[1]), op(X[1]), acc);
+                sum(acc, G[1][1]);
+                if constexpr (QUINTIC) {
+                    product(ng, op(G[1]), op(G[0]), acc);
+                    poly(G[0][1], acc, B[0][1]);
+                    put_t(B[0][1], ex);
+                    product(ng, op(G[0]), op(G[0]), acc);
+                    poly(G[0][0], acc, B[0][0]);
+                    product(ng, op(G[1]), op(G[1]), acc);
+                    poly(G[1][1], acc, B[1][1]);
+                    get(ex, B[1][0]);
+                } else {
+#pragma unroll
+                    for (int b = 0; b < 4; ++b) linear(G[b >> 1][b & 1], B[b >> 1][b & 1]);
+                }
+#pragma unroll
+                for (int b = 0; b < 4; ++b) {
+                    product(ng, xcol(b & 1), op(B[b >> 1]), acc);
+                    update(X[b >> 1][b & 1], acc);
+                }
+            }
+          }
+        };
+
+        // 128-tile, four waves of one block row each. Wave p evaluates blocks
+        // (p, p), (p, p + 1) and half the k range of (p, p + 2) (indices mod 4; the
+        // other half of that block comes, transposed, from wave p + 2), which
+        // is every block pair once and the same work for every wave. Block
+        // (p, p + 3) is the transpose of wave p - 1's (p - 1, p). k blocks run in
+        // an order that ends with the wave's own (the diagonal block of B is the
+        // largest: entering the chains last it rounds the fewest partial sums).
+        auto steps128 = [&](auto quintic) HM_INL {
+          if constexpr (SYM && NB == 4) {
+            constexpr bool QUINTIC = decltype(quintic)::value;  // c != 0
+            constexpr std::integral_constant<int, 16> n16{};
+            constexpr std::integral_constant<int, 8> n8{};
+            const int p = p0, p1 = (p + 1) & 3, p2 = (p + 2) & 3;
+            // the k block (offset from p) of group g: 2, 3, 1, 0, or the half's 1, 0
+            auto off16 = [](int g) HM_INL { return (g >> 2) < 2 ? 2 + (g >> 2) : 3 - (g >> 2); };
+            auto off8 = [](int g) HM_INL { return 1 - (g >> 2); };
+            auto row16 = [&](int J) HM_INL { return [&, J](int g) HM_INL { return xr[((J * 4 + ((p + off16(g)) & 3)) * S + (g & 3)) * 64 + lane]; }; };
+            auto row8 = [&](int J) HM_INL { return [&, J](int g) HM_INL { return xr[((J * 4 + ((p + off8(g)) & 3)) * S + (g & 3)) * 64 + lane]; }; };
+            auto op16 = [&](const f32x16 (&R)[4]) HM_INL { return [&](int g) HM_INL { return make_slot<OP>(R[off16(g)], g & 3); }; };
+            auto op8 = [&](const f32x16 (&R)[4]) HM_INL { return [&](int g) HM_INL { return make_slot<OP>(R[off8(g)], g & 3); }; };
+            auto xcol = [&](int j) HM_INL {
+                return [&, j](int g) HM_INL { return xc[(((p + off16(g)) & 3) * 4 + ((p + j) & 3)) * BLK + trd[g & 3]]; };
+            };
+            auto publish = [&](const f32x16 (&R)[4]) HM_INL {  // the wave's block row as operand slots
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+#pragma unroll
+                    for (int sl = 0; sl < S; ++sl) xr[((p * 4 + ((p + j) & 3)) * S + sl) * 64 + lane] = make_slot<OP>(R[j], sl);
+            };
+            // s_ex: blocks 0..3 for wave p + 1 ((p, p + 1) transposed, its R[3]), 4..7 for
+            // wave p + 2 (this wave's half of (p, p + 2), transposed)
+            auto offer = [&](const f32x16& r1, const f32x16& r2) HM_INL {
+                put_t(r1, s_ex + p1 * BLK);
+                put_t(r2, s_ex + (4 + p2) * BLK);
+                __syncthreads();
+            };
+            auto take = [&](f32x16 (&R)[4]) HM_INL {
+                f32x16 h;
+                get(s_ex + p * BLK, R[3]);
+                get(s_ex + (4 + p) * BLK, h);
+                R[2] += h;
+            };
+            // the block rows in rotated order: R[j] is block (p, p + j) (selected,
+            // not indexed: an index would send the tile to scratch)
+            f32x16 Xr[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                Xr[j] = X[0][j];
+                if (p == 1) Xr[j] = X[0][(j + 1) % 4];
+                if (p == 2) Xr[j] = X[0][(j + 2) % 4];
+                if (p == 3) Xr[j] = X[0][(j + 3) % 4];
+            }
+            for (int k = 0; k < args.K; ++k) {
+                f32x16 G[4], B[4], acc[NC];
+                publish(Xr);
+#pragma unroll
+                for (int j = 0; j < 4; ++j) put_t(Xr[j], xc + (p * 4 + ((p + j) & 3)) * BLK);
+                product(n16, op16(Xr), op16(Xr), acc);  // (the stores above land meanwhile)
+                sum(acc, G[0]);
+                __syncthreads();
+                product(n16, row16(p1), op16(Xr), acc);
+                sum(acc, G[1]);
+                product(n8, row8(p2), op8(Xr), acc);
+                sum(acc, G[2]);
+                offer(G[1], G[2]);  // (its barrier: every wave is done reading X from xr)
+                take(G);
+                if constexpr (QUINTIC) {
+                    publish(G);
+                    product(n16, op16(G), op16(G), acc);
+                    poly(G[0], acc, B[0]);
+                    __syncthreads();
+                    product(n16, row16(p1), op16(G), acc);
+                    poly(G[1], acc, B[1]);
+                    product(n8, row8(p2), op8(G), acc);
+                    sum(acc, B[2]);
+                    offer(B[1], B[2]);
+                    take(B);
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) B[2][r] = poly2(en, G[2][r], B[2][r]);
+                } else {
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) linear(G[j], B[j]);
+                }
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    product(n16, xcol(j), op16(B), acc);
+                    update(Xr[j], acc);
+                }
+                __syncthreads();  // xr, xc and the exchange blocks are rewritten next step
+            }
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                X[0][j] = Xr[j];
+                if (p == 1) X[0][j] = Xr[(j + 3) % 4];
+                if (p == 2) X[0][j] = Xr[(j + 2) % 4];
+                if (p == 3) X[0][j] = Xr[(j + 1) % 4];
+            }
+          }
+        };
+#undef HM_INL
+        constexpr std::true_type with_c{};
+        constexpr std::false_type without_c{};
+        if constexpr (SYM && NB == 2) {
+            if (args.c != 0.f) steps64(with_c);
+            else steps64(without_c);
+        } else if constexpr (SYM) {
+            if (args.c != 0.f) steps128(with_c);
+            else steps128(without_c);
+        } else {
         for (int k = 0; k < args.K; ++k) {
             u32x4 Xop[RB][NB][S];
 #pragma unroll
@@ -393,6 +629,8 @@ __global__ void __launch_bounds__(kThreads) ns_tiled_kernel(const KernelArgs arg
                     }
             }
             if constexpr (SHARED_ROWS) __syncthreads();  // xr / xc are rewritten next step
+        }
+
         }
 
         // ---- write back the unpadded part
