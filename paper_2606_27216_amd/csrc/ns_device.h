@@ -24,6 +24,14 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 // 16-byte vectors in the global address space (global_load / global_store)
 typedef __attribute__((address_space(1))) u32x4 gbl_u32x4;
 
+// The same widths where only the elements are aligned (rows of odd length, odd
+// leading dimensions): global memory takes them at any address.
+typedef u32x4 u32x4_any16 __attribute__((aligned(2)));
+typedef u32x2 u32x2_any16 __attribute__((aligned(2)));
+typedef uint32_t u32_any16 __attribute__((aligned(2)));
+typedef f32x4 f32x4_any32 __attribute__((aligned(4)));
+typedef __attribute__((address_space(1))) u32x4_any16 gbl_u32x4_any16;
+
 #define HM_DEV __device__ __forceinline__
 
 // The descriptor table is written before a launch and only read during it,
@@ -245,8 +253,13 @@ HM_DEV f32x4 load4(const void* base, int64_t gr, int64_t gc, int64_t ld, int64_t
         }
         f32x4 r = {0.f, 0.f, 0.f, 0.f};
         if (gr < rows) {
+            if (gc + 4 <= cols) {
+                const u32x2 w = *reinterpret_cast<const u32x2_any16*>(p);
+                return f32x4{__uint_as_float(w[0] << 16), __uint_as_float(w[0] & 0xffff0000u),
+                             __uint_as_float(w[1] << 16), __uint_as_float(w[1] & 0xffff0000u)};
+            }
 #pragma unroll
-            for (int e = 0; e < 4; ++e)
+            for (int e = 0; e < 3; ++e)
                 if (gc + e < cols) r[e] = __uint_as_float(((uint32_t)p[e]) << 16);
         }
         return r;
@@ -255,8 +268,9 @@ HM_DEV f32x4 load4(const void* base, int64_t gr, int64_t gc, int64_t ld, int64_t
         if (vec) return *reinterpret_cast<const f32x4*>(p);
         f32x4 r = {0.f, 0.f, 0.f, 0.f};
         if (gr < rows) {
+            if (gc + 4 <= cols) return *reinterpret_cast<const f32x4_any32*>(p);
 #pragma unroll
-            for (int e = 0; e < 4; ++e)
+            for (int e = 0; e < 3; ++e)
                 if (gc + e < cols) r[e] = p[e];
         }
         return r;
@@ -291,6 +305,10 @@ HM_DEV void store4(void* base, int64_t gr, int64_t gc, int64_t ld, int64_t rows,
             return;
         }
         if (gr < rows) {
+            if (gc + 4 <= cols) {
+                *reinterpret_cast<u32x2_any16*>(p) = u32x2{w0, w1};
+                return;
+            }
             const uint16_t h[4] = {(uint16_t)(w0 & 0xffffu), (uint16_t)(w0 >> 16), (uint16_t)(w1 & 0xffffu),
                                    (uint16_t)(w1 >> 16)};
 #pragma unroll
@@ -304,8 +322,12 @@ HM_DEV void store4(void* base, int64_t gr, int64_t gc, int64_t ld, int64_t rows,
             return;
         }
         if (gr < rows) {
+            if (gc + 4 <= cols) {
+                *reinterpret_cast<f32x4_any32*>(p) = v;
+                return;
+            }
 #pragma unroll
-            for (int e = 0; e < 4; ++e)
+            for (int e = 0; e < 3; ++e)
                 if (gc + e < cols) p[e] = v[e];
         }
     }

@@ -311,17 +311,39 @@ __global__ void __launch_bounds__((F16Shape<T, RB>::kThreads), (F16Shape<T, RB>:
 #pragma unroll
             for (int i = 0; i < NI; ++i) dst[i] = src[i * step];
         } else {
+            // edges of a matrix, or rows that are not 16-byte aligned: whole chunks at
+            // any address; the chunk that the last column cuts is the 16 bytes that
+            // end there, shifted down (six ragged matrices of 648 tiles took 59.6 us by
+            // 2-byte accesses and take 51.3 so)
+            const int64_t rem = L.cols - gc;  // columns from gc on
+            const int64_t back = rem < 8 && L.cols >= 8 ? 8 - rem : 0;
+            const bool any = rem > 0 && (rem >= 8 || L.cols >= 8);
+            const uint16_t* ptr = static_cast<const uint16_t*>(base) + gr0 * ld + gc - back;
 #pragma unroll
             for (int i = 0; i < NI; ++i) {
-                const int64_t gr = gr0 + RPI * i;
-                const uint16_t* ptr = static_cast<const uint16_t*>(base) + gr * ld + gc;
-                uint32_t h[8] = {0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u};
-                if (gr < L.rows) {
+                dst[i] = u32x4{};
+                if (any && gr0 + RPI * i < L.rows) dst[i] = *(const gbl_u32x4_any16*)(ptr + (int64_t)RPI * i * ld);
+            }
+            if (back > 0 && any) {
+                const uint32_t sh = 16u * (uint32_t)back;
 #pragma unroll
-                    for (int e = 0; e < 8; ++e)
-                        if (gc + e < L.cols) h[e] = ptr[e];
+                for (int i = 0; i < NI; ++i) {
+                    const uint64_t lo = dst[i][0] | (uint64_t)dst[i][1] << 32, hi = dst[i][2] | (uint64_t)dst[i][3] << 32;
+                    const uint64_t a = sh < 64 ? lo >> sh | hi << (64 - sh) : hi >> (sh - 64);
+                    const uint64_t b = sh < 64 ? hi >> sh : 0;
+                    dst[i] = u32x4{(uint32_t)a, (uint32_t)(a >> 32), (uint32_t)b, (uint32_t)(b >> 32)};
                 }
-                dst[i] = u32x4{h[0] | (h[1] << 16), h[2] | (h[3] << 16), h[4] | (h[5] << 16), h[6] | (h[7] << 16)};
+            } else if (rem > 0 && L.cols < 8) {  // a matrix narrower than a chunk
+#pragma unroll
+                for (int i = 0; i < NI; ++i) {
+                    const int64_t gr = gr0 + RPI * i;
+                    const uint16_t* p = static_cast<const uint16_t*>(base) + gr * ld + gc;
+                    if (gr < L.rows) {
+#pragma unroll
+                        for (int e = 0; e < 7; ++e)
+                            if (gc + e < L.cols) dst[i][e >> 1] |= (uint32_t)p[e] << (16 * (e & 1));
+                    }
+                }
             }
         }
     };
@@ -366,9 +388,16 @@ __global__ void __launch_bounds__((F16Shape<T, RB>::kThreads), (F16Shape<T, RB>:
                 const int64_t gr = gr0 + RPI * i;
                 uint16_t* ptr = static_cast<uint16_t*>(base) + gr * ld + gc;
                 if (gr < L.rows) {
-#pragma unroll
-                    for (int e = 0; e < 8; ++e)
-                        if (gc + e < L.cols) ptr[e] = (uint16_t)(v[i][e >> 1] >> (16 * (e & 1)));
+                    const int64_t rem = L.cols - gc;
+                    if (rem >= 8) {
+                        *(gbl_u32x4_any16*)ptr = v[i];
+                    } else if (rem > 0) {  // 4, 2 and 1 columns
+                        const uint32_t r = (uint32_t)rem;
+                        if (r & 4) *reinterpret_cast<u32x2_any16*>(ptr) = u32x2{v[i][0], v[i][1]};
+                        const uint32_t w = r & 4 ? v[i][2] : v[i][0], w1 = r & 4 ? v[i][3] : v[i][1];
+                        if (r & 2) *reinterpret_cast<u32_any16*>(ptr + (r & 4)) = w;
+                        if (r & 1) ptr[r & 6] = (uint16_t)(r & 2 ? w1 : w);
+                    }
                 }
             }
         }
