@@ -453,6 +453,64 @@ def _keep_alive(tensors, stream, dev):
             t.record_stream(stream)
 
 
+# Most matrices whose descriptors a call carries in its kernels' arguments
+# (kInlineMats of himuon_internal.h): such a call needs no table in memory.
+_INLINE_MATS = 32
+
+
+def _columns(*lists):
+    """Equally long lists of integers as one int64 array, and the address of each
+    list's part: one conversion for all arrays of a call."""
+    flat = []
+    for v in lists:
+        flat += v
+    buf = (ctypes.c_int64 * len(flat))(*flat)
+    base, step = ctypes.addressof(buf), 8 * len(lists[0])
+    return buf, [base + step * i for i in range(len(lists))]
+
+
+def _raw_stream(stream, dev):
+    """The hipStream_t of ``stream`` (None: torch's current stream of ``dev``)."""
+    import torch
+    return torch._C._cuda_getCurrentRawStream(dev.index) if stream is None else stream.cuda_stream
+
+
+def _check_matrices(inputs, outputs, code, dev):
+    """Raises what is wrong with a call's matrices."""
+    for x in inputs:
+        if x.dim() != 2 or not x.is_cuda or x.device != dev or _dtype_code(x) != code or x.stride(1) != 1:
+            raise ValueError("inputs must be 2-D row-major CUDA tensors of one dtype on one device")
+    if outputs is None:
+        return
+    if len(outputs) != len(inputs):
+        raise ValueError("inputs and outputs differ in length")
+    for x, y in zip(inputs, outputs):
+        if y.shape != x.shape or y.dtype != x.dtype or y.device != dev or y.stride(1) != 1:
+            raise ValueError("each output must match its input's shape, dtype and device")
+
+
+def _call_arrays(inputs, outputs, code, dev):
+    """(buffer, addresses of in_ptrs, out_ptrs, rows, cols, ld_in, ld_out) of a call over
+    these matrices, checked in the same pass."""
+    dt = inputs[0].dtype
+    ok = dev.type == "cuda" and len(outputs) == len(inputs)
+    rows, cols, lds, ldo = [], [], [], []
+    for x, y in zip(inputs, outputs):
+        shape, xs, ys = x.shape, x.stride(), y.stride()
+        if not ok or len(shape) != 2 or y.shape != shape or x.dtype is not dt or y.dtype is not dt or \
+                xs[1] != 1 or ys[1] != 1 or x.device != dev or y.device != dev:
+            ok = False
+            break
+        rows.append(shape[0])
+        cols.append(shape[1])
+        lds.append(xs[0])
+        ldo.append(ys[0])
+    if not ok:
+        _check_matrices(inputs, outputs, code, dev)
+        raise ValueError("inputs must be 2-D row-major CUDA tensors of one dtype on one device")
+    return _columns([x.data_ptr() for x in inputs], [y.data_ptr() for y in outputs], rows, cols, lds, ldo)
+
+
 def _dtype_code(t):
     import torch
     if t.dtype == torch.float32:
@@ -477,42 +535,39 @@ def ns_tiled(inputs, outputs=None, T=128, K=5, coeffs=QUINTIC, compute=COMPUTE_D
         raise ValueError("no matrices")
     code = _dtype_code(inputs[0])
     dev = inputs[0].device
-    for x in inputs:
-        if x.dim() != 2 or not x.is_cuda or x.device != dev or _dtype_code(x) != code or x.stride(1) != 1:
-            raise ValueError("inputs must be 2-D row-major CUDA tensors of one dtype on one device")
     fresh = []  # tensors allocated here for the call
     if outputs is None:
+        _check_matrices(inputs, None, code, dev)
         outputs = [torch.empty_like(x, memory_format=torch.contiguous_format) for x in inputs]
         fresh += outputs
     outputs = list(outputs)
-    if len(outputs) != len(inputs):
-        raise ValueError("inputs and outputs differ in length")
-    for x, y in zip(inputs, outputs):
-        if y.shape != x.shape or y.dtype != x.dtype or y.device != dev or y.stride(1) != 1:
-            raise ValueError("each output must match its input's shape, dtype and device")
+    buf, arrays = _call_arrays(inputs, outputs, code, dev)
     n = len(inputs)
-    a, b, c = coeffs
-    rows = [x.shape[0] for x in inputs]
-    cols = [x.shape[1] for x in inputs]
-    if workspace is None:
-        need = 0 if Tw is not None and Tw != T else \
-            himuon_ns_tiled_call_workspace_size(rows, cols, T, code, compute, K, a, b, c, chunk_budget_bytes)
-        # (a call that would be rejected still gets a table-sized workspace, so
-        # that the library reports the precise error)
-        workspace = torch.empty(max(need, himuon_ns_tiled_workspace_size(n)), dtype=torch.uint8, device=dev)
-        fresh.append(workspace)
-    if stream is None:
-        stream = torch.cuda.current_stream(dev)
-    ptrs = ([x.data_ptr() for x in inputs], [y.data_ptr() for y in outputs], rows, cols,
-            [x.stride(0) for x in inputs], [y.stride(0) for y in outputs])
-    ws = (workspace.data_ptr(), workspace.numel() * workspace.element_size(), chunk_budget_bytes, stream.cuda_stream)
-    if Tw is None or Tw == T:
-        st = himuon_ns_tiled(n, *ptrs, T, K, a, b, c, code, compute, *ws)
+    a, b, c = map(float, coeffs)
+    T, K, compute, budget = int(T), int(K), int(compute), int(chunk_budget_bytes)
+    square = Tw is None or Tw == T
+    raw = _raw_stream(stream, dev)
+    if workspace is None and square and n <= _INLINE_MATS and \
+            (T in (32, 64, 128) or (T == 256 and code == BF16 and compute in (COMPUTE_DEFAULT, COMPUTE_F16))):
+        # a fused kernel with its table in the arguments: no workspace to allocate
+        st = lib().himuon_ns_tiled_noalloc(n, *arrays, T, K, a, b, c, code, compute, budget, raw or None)
     else:
-        st = himuon_ns_tiled_hw(n, *ptrs, T, Tw, K, a, b, c, code, compute, *ws)
+        if workspace is None:
+            need = 0 if not square else \
+                lib().himuon_ns_tiled_call_workspace_size(n, arrays[2], arrays[3], T, code, compute, K, a, b, c, budget)
+            # (a call that would be rejected still gets a table-sized workspace, so
+            # that the library reports the precise error)
+            workspace = torch.empty(max(need, himuon_ns_tiled_workspace_size(n)), dtype=torch.uint8, device=dev)
+            fresh.append(workspace)
+        ws = (workspace.data_ptr(), workspace.numel() * workspace.element_size(), budget, raw or None)
+        if square:
+            st = lib().himuon_ns_tiled(n, *arrays, T, K, a, b, c, code, compute, *ws)
+        else:
+            st = lib().himuon_ns_tiled_hw(n, *arrays, T, int(Tw), K, a, b, c, code, compute, *ws)
     if st != OK:
-        raise HimuonError(st, "himuon_ns_tiled" if Tw is None or Tw == T else "himuon_ns_tiled_hw")
-    _keep_alive(fresh, stream, dev)
+        raise HimuonError(st, "himuon_ns_tiled" if square else "himuon_ns_tiled_hw")
+    if stream is not None:
+        _keep_alive(fresh, stream, dev)
     return outputs
 
 
@@ -529,40 +584,29 @@ def ns_gemm(inputs, outputs=None, T=0, K=5, coeffs=QUINTIC, compute=COMPUTE_DEFA
         raise ValueError("no matrices")
     code = _dtype_code(inputs[0])
     dev = inputs[0].device
-    for x in inputs:
-        if x.dim() != 2 or not x.is_cuda or x.device != dev or _dtype_code(x) != code or x.stride(1) != 1:
-            raise ValueError("inputs must be 2-D row-major CUDA tensors of one dtype on one device")
     fresh = []  # tensors allocated here for the call
     if outputs is None:
+        _check_matrices(inputs, None, code, dev)
         outputs = [torch.empty_like(x, memory_format=torch.contiguous_format) for x in inputs]
         fresh += outputs
     outputs = list(outputs)
-    if len(outputs) != len(inputs):
-        raise ValueError("inputs and outputs differ in length")
-    for x, y in zip(inputs, outputs):
-        if y.shape != x.shape or y.dtype != x.dtype or y.device != dev or y.stride(1) != 1:
-            raise ValueError("each output must match its input's shape, dtype and device")
+    buf, arrays = _call_arrays(inputs, outputs, code, dev)
     n = len(inputs)
-    a, b, c = coeffs
-    rows = [x.shape[0] for x in inputs]
-    cols = [x.shape[1] for x in inputs]
-    Th, Tw = int(T), int(T if Tw is None else Tw)
-    need = himuon_ns_gemm_hw_workspace_size(rows, cols, Th, Tw, code, compute, K, a, b, c, chunk_budget_bytes)
+    a, b, c = map(float, coeffs)
+    Th, Tw, K, compute, budget = int(T), int(T if Tw is None else Tw), int(K), int(compute), int(chunk_budget_bytes)
+    need = lib().himuon_ns_gemm_hw_workspace_size(n, arrays[2], arrays[3], Th, Tw, code, compute, K, a, b, c, budget)
     if need == 0:
         raise HimuonError(ERR_INVALID_ARG, "himuon_ns_gemm_hw_workspace_size")
     if workspace is None:
         workspace = torch.empty(need, dtype=torch.uint8, device=dev)
         fresh.append(workspace)
-    if stream is None:
-        stream = torch.cuda.current_stream(dev)
-    st = himuon_ns_gemm_hw(
-        n, [x.data_ptr() for x in inputs], [y.data_ptr() for y in outputs], rows, cols,
-        [x.stride(0) for x in inputs], [y.stride(0) for y in outputs],
-        Th, Tw, K, a, b, c, code, compute, workspace.data_ptr(), workspace.numel() * workspace.element_size(),
-        chunk_budget_bytes, stream.cuda_stream)
+    st = lib().himuon_ns_gemm_hw(n, *arrays, Th, Tw, K, a, b, c, code, compute, workspace.data_ptr(),
+                                 workspace.numel() * workspace.element_size(), budget,
+                                 _raw_stream(stream, dev) or None)
     if st != OK:
         raise HimuonError(st, "himuon_ns_gemm_hw")
-    _keep_alive(fresh, stream, dev)
+    if stream is not None:
+        _keep_alive(fresh, stream, dev)
     return outputs
 
 
@@ -579,32 +623,50 @@ def step(weights, grads, moms, T=512, K=5, coeffs=QUINTIC, lr=0.02, momentum=0.9
         raise ValueError("weights, grads and moms must be equally long, non-empty lists")
     code = _dtype_code(weights[0])
     dev = weights[0].device
+    dt = weights[0].dtype
+    ok = dev.type == "cuda"
+    rows, cols, lds = [], [], []
     for w, g, m in zip(weights, grads, moms):
-        for x in (w, g, m):
-            if x.dim() != 2 or not x.is_cuda or x.device != dev or _dtype_code(x) != code or x.stride(1) != 1:
-                raise ValueError("matrices must be 2-D row-major CUDA tensors of one dtype on one device")
-        if g.shape != w.shape or m.shape != w.shape or g.stride(0) != w.stride(0) or m.stride(0) != w.stride(0):
-            raise ValueError("W, G and M of a matrix must share shape and row stride")
-    a, b, c = coeffs
-    rows = [w.shape[0] for w in weights]
-    cols = [w.shape[1] for w in weights]
-    need = himuon_step_workspace_size(rows, cols, T, code, compute, K, a, b, c, chunk_budget_bytes)
-    if need == 0:
-        raise HimuonError(ERR_INVALID_ARG, "himuon_step_workspace_size")
+        shape, ws = w.shape, w.stride()
+        if not ok or len(shape) != 2 or ws[1] != 1 or g.shape != shape or m.shape != shape or g.stride() != ws or \
+                m.stride() != ws or w.dtype is not dt or g.dtype is not dt or m.dtype is not dt or \
+                w.device != dev or g.device != dev or m.device != dev:
+            ok = False
+            break
+        rows.append(shape[0])
+        cols.append(shape[1])
+        lds.append(ws[0])
+    if not ok:
+        for w, g, m in zip(weights, grads, moms):
+            for x in (w, g, m):
+                if x.dim() != 2 or not x.is_cuda or x.device != dev or _dtype_code(x) != code or x.stride(1) != 1:
+                    raise ValueError("matrices must be 2-D row-major CUDA tensors of one dtype on one device")
+            if g.shape != w.shape or m.shape != w.shape or g.stride(0) != w.stride(0) or m.stride(0) != w.stride(0):
+                raise ValueError("W, G and M of a matrix must share shape and row stride")
+        raise ValueError("matrices must be 2-D row-major CUDA tensors of one dtype on one device")
+    a, b, c = map(float, coeffs)
+    n, T, K, compute, budget = len(weights), int(T), int(K), int(compute), int(chunk_budget_bytes)
+    buf, arrays = _columns([w.data_ptr() for w in weights], [g.data_ptr() for g in grads],
+                           [m.data_ptr() for m in moms], rows, cols, lds)
+
+    def size():
+        need = lib().himuon_step_workspace_size(n, arrays[3], arrays[4], T, code, compute, K, a, b, c, budget)
+        if need == 0:
+            raise HimuonError(ERR_INVALID_ARG, "himuon_step_workspace_size")
+        return need
+
     fresh = []
     if workspace is None:
-        workspace = torch.empty(need, dtype=torch.uint8, device=dev)
+        workspace = torch.empty(size(), dtype=torch.uint8, device=dev)
         fresh.append(workspace)
-    if stream is None:
-        stream = torch.cuda.current_stream(dev)
-    st = himuon_step(
-        len(weights), [w.data_ptr() for w in weights], [g.data_ptr() for g in grads], [m.data_ptr() for m in moms],
-        rows, cols, [w.stride(0) for w in weights], T, K, a, b, c, lr, momentum, weight_decay, nesterov, scale_c,
-        code, compute, workspace.data_ptr(), workspace.numel() * workspace.element_size(), chunk_budget_bytes,
-        stream.cuda_stream)
+    st = lib().himuon_step(n, *arrays, T, K, a, b, c, float(lr), float(momentum), float(weight_decay),
+                           int(bool(nesterov)), float(scale_c), code, compute, workspace.data_ptr(),
+                           workspace.numel() * workspace.element_size(), budget, _raw_stream(stream, dev) or None)
     if st != OK:
+        size()  # (a call without a plan is reported as that)
         raise HimuonError(st, "himuon_step")
-    _keep_alive(fresh, stream, dev)
+    if stream is not None:
+        _keep_alive(fresh, stream, dev)
     return weights
 
 
