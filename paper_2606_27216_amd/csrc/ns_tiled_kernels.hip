@@ -666,6 +666,115 @@ __global__ void __launch_bounds__(kThreads) ns_tiled_kernel(const KernelArgs arg
     }
 }
 
+// fp32 32-tiles, one workgroup of four waves per tile, for calls that leave most
+// of the chip idle. A 32-tile's step is a serial chain in one wave: 48 fp32 MFMAs
+// of 64 cycles and the sums between them. The four accumulator chains of a
+// product (one per element e of an operand slot) are independent: here
+// wave w runs chain w, which reads only its elements 4s + w of the row pieces, and
+// holds only those. The partial sums go through LDS, each wave taking the
+// registers of its own elements from all four chains, so every sum has the terms
+// and the order of the one-wave kernel and the result its bits.
+// A 256 x 256 matrix (64 tiles), K = 5: 10.1 us a call, 14.1 with one wave per tile.
+__global__ void __launch_bounds__(kThreads) ns_tiled_f32_split32_kernel(const KernelArgs args)
+{
+    __shared__ f32x4 s_ex[2][4][4][64];  // [exchange parity][chain][element][lane]
+    __shared__ float s_x[32 * 33];       // X by rows
+    const int lane = threadIdx.x & 63;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int li = lane & 31, lh = lane >> 5;
+    const int64_t tile = args.tile_begin + blockIdx.x;
+    const ConstDesc& d = desc_table(args)[find_matrix_from(args, tile, 0)];
+    const uint32_t lt = (uint32_t)(tile - d.tile_begin);
+    const uint32_t tc = (uint32_t)d.tiles_c;
+    const uint32_t tr = lt / tc;
+    const int64_t row0 = (int64_t)tr * 32, col0 = (int64_t)(lt - tr * tc) * 32;
+    const bool vin = row0 + 32 <= d.rows && col0 + 32 <= d.cols && (d.flags & MAT_VEC_IN);
+
+    // every wave reads the tile and normalises it as the one-wave kernel does
+    f32x16 X;
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+        const f32x4 v = load4<Storage::F32>(d.in, row0 + li, col0 + 8 * g + 4 * lh, d.ld_in, d.rows, d.cols, vin);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) X[4 * g + e] = v[e];
+    }
+    float mx = 0.f;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) mx = fmaxf(mx, fabsf(X[v]));
+    mx = wave_max(mx);
+    int ex = 0;
+    (void)frexpf(mx, &ex);
+    const float s1 = ldexpf(1.f, -(ex / 2)), s2 = ldexpf(1.f, -(ex - ex / 2));
+    float ss = 0.f;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+        const float y = X[v] * s1 * s2;
+        X[v] = y;
+        ss = fmaf(y, y, ss);
+    }
+    ss = wave_sum(ss);
+    const ExactNorm en = exact_norm(ss, args.b, args.c);
+    X *= en.scale;
+    auto mine = [&](const f32x16& v, int s) -> float {
+        return w == 0 ? v[4 * s] : (w == 1 ? v[4 * s + 1] : (w == 2 ? v[4 * s + 2] : v[4 * s + 3]));
+    };
+    float x[4];
+#pragma unroll
+    for (int s = 0; s < 4; ++s) x[s] = mine(X, s);
+
+    // the wave's elements of the sum of the four chains
+    auto reduce = [&](const f32x16& acc, int parity, float (&v)[4]) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) s_ex[parity][w][e][lane] = f32x4{acc[e], acc[4 + e], acc[8 + e], acc[12 + e]};
+        __syncthreads();
+        const f32x4 c0 = s_ex[parity][0][w][lane], c1 = s_ex[parity][1][w][lane];
+        const f32x4 c2 = s_ex[parity][2][w][lane], c3 = s_ex[parity][3][w][lane];
+        const f32x4 t = (c0 + c1) + (c2 + c3);
+#pragma unroll
+        for (int s = 0; s < 4; ++s) v[s] = t[s];
+    };
+    auto chain = [&](const float (&a)[4], const float (&b)[4]) -> f32x16 {
+        f32x16 acc = {};
+#pragma unroll
+        for (int s = 0; s < 4; ++s) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[s], b[s], acc, 0, 0, 0);
+        return acc;
+    };
+    int parity = 0;  // (an exchange buffer is rewritten two barriers after it was read)
+    for (int k = 0; k < args.K; ++k) {
+        // (read again behind the barrier of the first exchange; last read before
+        // the barrier of the previous step's last one)
+#pragma unroll
+        for (int s = 0; s < 4; ++s) s_x[li * 33 + 8 * s + 4 * lh + w] = x[s];
+        float g[4], b[4], xc[4];
+        reduce(chain(x, x), parity, g);
+        parity ^= 1;
+#pragma unroll
+        for (int s = 0; s < 4; ++s) xc[s] = s_x[(8 * s + 4 * lh + w) * 33 + li];
+        if (args.c != 0.f) {
+            float q[4];
+            reduce(chain(g, g), parity, q);
+            parity ^= 1;
+#pragma unroll
+            for (int s = 0; s < 4; ++s) b[s] = poly2(en, g[s], q[s]);
+        } else {
+#pragma unroll
+            for (int s = 0; s < 4; ++s) b[s] = fmaf(en.bh, g[s], en.bl * g[s]);
+        }
+        float bx[4];
+        reduce(chain(xc, b), parity, bx);
+        parity ^= 1;
+#pragma unroll
+        for (int s = 0; s < 4; ++s) x[s] = fmaf(args.a, x[s], bx[s]);
+    }
+    __syncthreads();  // (K = 0, in place: every wave has read the tile)
+    float* const out = static_cast<float*>(d.out) + (row0 + li) * d.ld_out + col0 + 4 * lh + w;
+    if (row0 + li < d.rows) {
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+            if (col0 + 8 * s + 4 * lh + w < d.cols) out[8 * s] = x[s] * en.out;
+    }
+}
+
 // ----------------------------------------------------------------- launch
 
 constexpr int kMaxDevices = 64;
@@ -698,6 +807,11 @@ hipError_t launch_one(const KernelArgs& args, hipStream_t stream)
     return hipGetLastError();
 }
 
+// us a call, K = 5, split / one wave: 256 tiles 10.3 / 14, 512 11.5 / 14.2, 768
+// 15.2 / 14.3, 1024 17.9 / 14.9: two tiles per CU hide each other's exchanges, from
+// three on the one-wave tiles use the four SIMDs better.
+constexpr int64_t kSplit32Tiles = 512;
+
 // Kernel choice per tile size: rows of a T <= 64 tile stay in one wave (no
 // workgroup barriers); a T = 128 tile is split over four waves.
 template <Storage ST, Operand OP>
@@ -709,6 +823,13 @@ hipError_t launch_T(int T, const KernelArgs& args, hipStream_t stream)
         case 64: return launch_one<64, 2, ST, OP, true>(args, stream);
         case 128: return launch_one<128, 1, ST, OP, true>(args, stream);
         default: return hipErrorInvalidValue;
+        }
+    }
+    if constexpr (OP == Operand::F32) {
+        const int64_t n = args.tile_end - args.tile_begin;
+        if (T == 32 && n > 0 && n <= kSplit32Tiles) {
+            hipLaunchKernelGGL(ns_tiled_f32_split32_kernel, dim3((unsigned)n), dim3(kThreads), 0, stream, args);
+            return hipGetLastError();
         }
     }
     switch (T) {
