@@ -342,6 +342,11 @@ MatDesc make_desc(const void* in, void* out, int64_t rows, int64_t cols, int64_t
     return d;
 }
 
+bool whole_tiles(const MatDesc& d, int Th, int Tw)
+{
+    return d.rows % Th == 0 && d.cols % Tw == 0 && d.flags == (MAT_VEC_IN | MAT_VEC_OUT);
+}
+
 KernelArgs make_kernel_args(const MatDesc* descs, int64_t n_mats, int K, float a, float b, float c)
 {
     KernelArgs ka{};
@@ -444,10 +449,12 @@ int run_tiled(int64_t n_mats, const void* const* in_ptrs, void* const* out_ptrs,
     // ---- descriptor table
     std::vector<MatDesc> descs((size_t)n_mats);
     int64_t next = 0;
+    bool whole = true;
     for (int64_t m = 0; m < n_mats; ++m) {
         descs[(size_t)m] = make_desc(in_ptrs[m], out_ptrs[m], rows[m], cols[m], ld_in ? ld_in[m] : cols[m],
                                      ld_out ? ld_out[m] : cols[m], next, T, dtype,
                                      opt_host ? opt_host[m].mom : nullptr);
+        whole = whole && whole_tiles(descs[(size_t)m], T, T);
         next += ceil_div(rows[m], T) * ceil_div(cols[m], T);
     }
 
@@ -471,6 +478,7 @@ int run_tiled(int64_t n_mats, const void* const* in_ptrs, void* const* out_ptrs,
         KernelArgs ka = make_kernel_args(static_cast<const MatDesc*>(workspace), n_mats, K, a, b, c);
         ka.odescs = otab;
         ka.step = opt_host ? 1 : 0;
+        ka.whole_tiles = whole ? 1 : 0;
         if (inl) set_inline_tables(ka, descs.data(), opt_host, n_mats);
         ka.beta = beta;
         ka.decay = decay;

@@ -62,6 +62,7 @@ struct KernelArgs {
     int32_t nesterov;
     int64_t tile_begin;
     int64_t tile_end;
+    int32_t whole_tiles;  // 1: no tile of the call is cut by its matrix, and all rows are 16-byte aligned
     int32_t n_mats;
     int32_t K;
     float a, b, c;
@@ -119,6 +120,8 @@ int plan_tiled_chunks(int64_t n_mats, const int64_t* rows, const int64_t* cols, 
                       size_t chunk_budget_bytes, int64_t* total, int64_t* n_chunks);
 MatDesc make_desc(const void* in, void* out, int64_t rows, int64_t cols, int64_t ld_in, int64_t ld_out,
                   int64_t tile_begin, int Tw, int dtype, const void* mom);
+// True when every tile of the matrix is whole and its rows are aligned, in and out.
+bool whole_tiles(const MatDesc& d, int Th, int Tw);
 KernelArgs make_kernel_args(const MatDesc* descs, int64_t n_mats, int K, float a, float b, float c);
 // Copies the tables of a call of at most kInlineMats matrices into the
 // arguments (descs, odescs become null; `opt` may be null).

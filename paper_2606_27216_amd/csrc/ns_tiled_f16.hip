@@ -145,7 +145,11 @@ template <int T, int RB> struct F16Shape {
 // the staging turns the loaded G and M into the stored new M and the
 // lookahead, and the write-back turns U into the decayed, tau-scaled update
 // of the loaded W. Without OPT the kernel is the map alone.
-template <int T, int RB, int CMODE, bool OPT>
+// EDGE: tiles may be cut by the matrix or have unaligned rows. A 128-tile call
+// whose tiles are all whole and aligned (KernelArgs::whole_tiles) runs a kernel
+// without that code (see launch_f16): beside it the compiler allots the registers
+// of the main path differently.
+template <int T, int RB, int CMODE, bool OPT, bool EDGE>
 __global__ void __launch_bounds__((F16Shape<T, RB>::kThreads), (F16Shape<T, RB>::kMinWavesPerEU)) ns_tiled_f16_kernel(const KernelArgs args)
 {
     constexpr Storage ST = Storage::BF16;
@@ -270,10 +274,14 @@ __global__ void __launch_bounds__((F16Shape<T, RB>::kThreads), (F16Shape<T, RB>:
         const uint32_t tr = lt / tc;
         L.row0 = (int64_t)tr * T;
         L.col0 = (int64_t)(lt - tr * tc) * T;
-        const bool full = L.row0 + T <= L.rows && L.col0 + T <= L.cols;
-        const int32_t fl = D.flags;  // (read unconditionally: no dependent scalar load)
-        L.vin = full & ((fl & MAT_VEC_IN) != 0);
-        L.vout = full & ((fl & MAT_VEC_OUT) != 0);
+        if constexpr (EDGE) {
+            const bool full = L.row0 + T <= L.rows && L.col0 + T <= L.cols;
+            const int32_t fl = D.flags;  // (read unconditionally: no dependent scalar load)
+            L.vin = full & ((fl & MAT_VEC_IN) != 0);
+            L.vout = full & ((fl & MAT_VEC_OUT) != 0);
+        } else {
+            L.vin = L.vout = 1;
+        }
         if constexpr (OPT) {
             const ConstOpt& O = opt_table(args)[mhint];
             L.mom = O.mom;
@@ -305,7 +313,7 @@ __global__ void __launch_bounds__((F16Shape<T, RB>::kThreads), (F16Shape<T, RB>:
     auto load_rows = [&](const TileLoc& L, const void* base, int64_t ld, bool vec, u32x4 (&dst)[NI]) {
         const int64_t gr0 = L.row0 + 32 * p0 + io_row;
         const int64_t gc = L.col0 + 8 * io_cc;
-        if (vec) {  // whole tile inside, 16-byte aligned: straight vector loads
+        if (!EDGE || vec) {  // whole tile inside, 16-byte aligned: straight vector loads
             const gbl_u32x4* src = (const gbl_u32x4*)(static_cast<const uint16_t*>(base) + gr0 * ld + gc);
             const int64_t step = (int64_t)RPI * ld / 8;  // u32x4 per RPI rows
 #pragma unroll
@@ -333,16 +341,19 @@ __global__ void __launch_bounds__((F16Shape<T, RB>::kThreads), (F16Shape<T, RB>:
                     const uint64_t b = sh < 64 ? hi >> sh : 0;
                     dst[i] = u32x4{(uint32_t)a, (uint32_t)(a >> 32), (uint32_t)b, (uint32_t)(b >> 32)};
                 }
-            } else if (rem > 0 && L.cols < 8) {  // a matrix narrower than a chunk
+            } else if (rem > 0 && L.cols < 8) {  // a matrix narrower than a chunk: 4, 2 and 1 columns
+                const uint32_t r = (uint32_t)rem;
+                const uint16_t* p = static_cast<const uint16_t*>(base) + gr0 * ld + gc;
 #pragma unroll
-                for (int i = 0; i < NI; ++i) {
-                    const int64_t gr = gr0 + RPI * i;
-                    const uint16_t* p = static_cast<const uint16_t*>(base) + gr * ld + gc;
-                    if (gr < L.rows) {
-#pragma unroll
-                        for (int e = 0; e < 7; ++e)
-                            if (gc + e < L.cols) dst[i][e >> 1] |= (uint32_t)p[e] << (16 * (e & 1));
-                    }
+                for (int i = 0; i < NI; ++i, p += (int64_t)RPI * ld) {
+                    if (gr0 + RPI * i >= L.rows) continue;
+                    u32x2 q = {};
+                    uint32_t t = 0, o = 0;
+                    if (r & 4) q = *reinterpret_cast<const u32x2_any16*>(p);
+                    if (r & 2) t = *reinterpret_cast<const u32_any16*>(p + (r & 4));
+                    if (r & 1) o = p[r & 6];
+                    const uint32_t w0 = r & 2 ? t : o, w1 = r & 2 ? o : 0u;
+                    dst[i] = r & 4 ? u32x4{q[0], q[1], w0, w1} : u32x4{w0, w1, 0u, 0u};
                 }
             }
         }
@@ -377,7 +388,7 @@ __global__ void __launch_bounds__((F16Shape<T, RB>::kThreads), (F16Shape<T, RB>:
     auto put_rows = [&](const TileLoc& L, void* base, int64_t ld, bool vec, const u32x4 (&v)[NI]) {
         const int64_t gr0 = L.row0 + 32 * p0 + io_row;
         const int64_t gc = L.col0 + 8 * io_cc;
-        if (vec) {
+        if (!EDGE || vec) {
             gbl_u32x4* dst = (gbl_u32x4*)(static_cast<uint16_t*>(base) + gr0 * ld + gc);
             const int64_t step = (int64_t)RPI * ld / 8;
 #pragma unroll
@@ -1453,8 +1464,8 @@ __global__ void __launch_bounds__((F16Shape<T, RB>::kThreads), (F16Shape<T, RB>:
 
 constexpr int kMaxDevices = 64;
 
-template <int T, int RB, int CMODE, bool OPT = false>
-hipError_t launch_f16(const KernelArgs& args, hipStream_t stream)
+template <int T, int RB, int CMODE, bool OPT, bool EDGE>
+hipError_t launch_f16_kernel(const KernelArgs& args, hipStream_t stream)
 {
     constexpr int TPW = F16Shape<T, RB>::TPW;
     constexpr int NT = F16Shape<T, RB>::kThreads;
@@ -1466,7 +1477,7 @@ hipError_t launch_f16(const KernelArgs& args, hipStream_t stream)
     int cap = resident[dev].load(std::memory_order_relaxed);
     if (cap == 0) {
         int per_cu = 0, cus = 0;
-        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, ns_tiled_f16_kernel<T, RB, CMODE, OPT>, NT, 0);
+        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, ns_tiled_f16_kernel<T, RB, CMODE, OPT, EDGE>, NT, 0);
         if (e != hipSuccess) return e;
         e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
         if (e != hipSuccess) return e;
@@ -1477,8 +1488,19 @@ hipError_t launch_f16(const KernelArgs& args, hipStream_t stream)
     if (n <= 0) return hipSuccess;
     const int64_t groups = (n + TPW - 1) / TPW;
     const int grid = (int)(groups < cap ? groups : cap);
-    hipLaunchKernelGGL((ns_tiled_f16_kernel<T, RB, CMODE, OPT>), dim3(grid), dim3(NT), 0, stream, args);
+    hipLaunchKernelGGL((ns_tiled_f16_kernel<T, RB, CMODE, OPT, EDGE>), dim3(grid), dim3(NT), 0, stream, args);
     return hipGetLastError();
+}
+
+template <int T, int RB, int CMODE, bool OPT = false> hipError_t launch_f16(const KernelArgs& args, hipStream_t stream)
+{
+    // (c > 0, the coefficients in use, at T = 128: against the start of the unaligned
+    // accesses its kernel with the edge code ran at 0.976, 0.973 (64 tiles) and 0.996
+    // (step), without it 1.005, 1.015 and 1.046; T = 64 0.999 with and 0.985 without)
+    if constexpr (CMODE == 0 && T == 128) {
+        if (args.whole_tiles) return launch_f16_kernel<T, RB, CMODE, OPT, false>(args, stream);
+    }
+    return launch_f16_kernel<T, RB, CMODE, OPT, true>(args, stream);
 }
 
 }  // namespace

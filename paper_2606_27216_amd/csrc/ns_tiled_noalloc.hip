@@ -97,11 +97,13 @@ extern "C" int himuon_ns_tiled_noalloc(int64_t n_mats, const void* const* in_ptr
     MatDesc inline_descs[himuon::kInlineMats];
     DescWords words;
     int64_t next = 0;
+    bool whole = true;
     if (inl) {
         for (int64_t m = 0; m < n_mats; ++m) {
             inline_descs[m] = himuon::make_desc(in_ptrs[m], out_ptrs[m], rows[m], cols[m],
                                                 ld_in ? ld_in[m] : cols[m], ld_out ? ld_out[m] : cols[m], next, T,
                                                 dtype, nullptr);
+            whole = whole && himuon::whole_tiles(inline_descs[m], T, T);
             next += ceil_div(rows[m], T) * ceil_div(cols[m], T);
         }
     }
@@ -114,6 +116,7 @@ extern "C" int himuon_ns_tiled_noalloc(int64_t n_mats, const void* const* in_ptr
                                                 ld_in ? ld_in[m] : cols[m], ld_out ? ld_out[m] : cols[m], next, T,
                                                 dtype, nullptr);
             memcpy(&words.w[j * kWordsPerDesc], &d, sizeof(MatDesc));
+            whole = whole && himuon::whole_tiles(d, T, T);
             next += ceil_div(rows[m], T) * ceil_div(cols[m], T);
         }
         hipLaunchKernelGGL(upload_descs, dim3(1), dim3(kPerUpload * kWordsPerDesc), 0, hs, words,
@@ -123,6 +126,7 @@ extern "C" int himuon_ns_tiled_noalloc(int64_t n_mats, const void* const* in_ptr
     }
     if (status == HIMUON_OK) {
         himuon::KernelArgs ka = himuon::make_kernel_args(static_cast<const MatDesc*>(table), n_mats, K, a, b, c);
+        ka.whole_tiles = whole ? 1 : 0;
         if (inl) himuon::set_inline_tables(ka, inline_descs, nullptr, n_mats);
         status = himuon::launch_chunks(T, st, opnd, ka, total, n_chunks, hs);
     }
