@@ -218,7 +218,7 @@ int himuon_ns_tiled_noalloc(int64_t n_mats,
                             void* stream);
 
 /*
- * Phi_K through library GEMMs: the full-matrix branch and large tiles.
+ * Phi_K through batched products: the full-matrix branch and large tiles.
  *
  * T = 0: Phi_K of every whole matrix (the full-matrix branch, Sec. 4.4.3).
  *        A matrix with more rows than columns is worked on transposed,
@@ -301,6 +301,8 @@ int himuon_ns_gemm_hw(int64_t n_mats,
  * library's leading heuristic candidates (up to 8), by timing each on the
  * workspace's buffers on `stream`; later calls on this device use the
  * choice. Results never depend on it beyond the rounding of the GEMMs.
+ * Products that run on this library's own kernels (16-bit operands, c != 0,
+ * all but narrow problems) have nothing to pick: the call validates and returns.
  *
  * Arguments as himuon_ns_gemm_workspace_size, plus workspace (at least that
  * many bytes; its contents are overwritten) and stream. Unlike the compute
