@@ -85,7 +85,7 @@ HM_DEV uint32_t lds_offset(const void* p)
 HM_DEV void dma16(uint32_t dst, uint32_t voff, uint64_t base)
 {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(dst), "v"(voff), "s"(base)
-                 : "memory");
+                 : "m0", "memory");
 }
 
 // Waits until at most N of this wave's DMA are in flight and its LDS reads
