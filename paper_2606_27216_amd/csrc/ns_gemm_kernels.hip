@@ -77,8 +77,10 @@ template <> struct OpType<GemmOperand::F32> { typedef float T; };
 template <> struct OpType<GemmOperand::F16> { typedef _Float16 T; };
 template <> struct OpType<GemmOperand::BF16> { typedef __bf16 T; };
 
-// Part j of problem p sums the squares of rows [j*rpp, (j+1)*rpp) of its
-// block, each thread over a fixed set of columns, then a fixed-order tree.
+// Part j of problem p sums the squares of its block's 8-column chunks
+// [j*per, (j+1)*per), counted row by row, each thread over a fixed set of them,
+// then a fixed-order tree. (Whole rows per part left a narrow matrix with as few
+// parts as it has rows or columns.)
 // (OPT: the momentum update M <- beta M + G of every element happens here,
 // once, and the sum is over the lookahead gradient formed from its stored
 // value, exactly as the gather forms it.)
@@ -87,17 +89,17 @@ __global__ void __launch_bounds__(kThreads) gemm_norm_partials(const GemmProb* p
                                                                const OptArgs o)
 {
     const GemmProb P = probs[blockIdx.y];
-    const int rpp = (P.h + nparts - 1) / nparts;
-    const int r0 = (int)blockIdx.x * rpp;
-    const int r1 = min(P.h, r0 + rpp);
     double acc = 0.0;
-    // the part's rows x 8-column chunks, flattened: element e = (row, chunk)
-    // (32-bit: a part is about 8192 elements or one row)
-    const uint32_t cpr = (uint32_t)(P.w + 7) / 8u;
-    const uint32_t n_e = (uint32_t)max(r1 - r0, 0) * cpr;
+    const uint32_t cpr = (uint32_t)(P.w + 7) / 8u;  // chunks per row
+    const int64_t total = (int64_t)P.h * cpr, per = (total + nparts - 1) / nparts;
+    const int64_t first = min(total, per * (int64_t)blockIdx.x);
+    // (32-bit from here: a part is about 1024 chunks)
+    const uint32_t n_e = (uint32_t)(min(total, first + per) - first);
+    const int r0 = (int)(first / cpr);
+    const uint32_t c0 = (uint32_t)(first - (int64_t)r0 * cpr);
     for (uint32_t e0 = threadIdx.x; e0 < n_e; e0 += kThreads) {
-        const uint32_t dr = e0 / cpr;
-        const int r = r0 + (int)dr, c = 8 * (int)(e0 - dr * cpr);
+        const uint32_t dr = (c0 + e0) / cpr;
+        const int r = r0 + (int)dr, c = 8 * (int)(c0 + e0 - dr * cpr);
         const int64_t rowoff = (P.row0 + r) * P.ld_in + P.col0;
         const int nv = min(8, P.w - c);
         const bool vec = (P.vec & GEMM_VEC_IN) && nv == 8;

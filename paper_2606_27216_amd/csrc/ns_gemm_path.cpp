@@ -68,10 +68,14 @@ struct Group {
     size_t bytes_pp = 0;   // iterate buffers per problem (X, X', A, B)
 };
 
-// Norm partials per problem: about 8192 elements each, in whole rows. A pass
-// over three 6144 x 2048 matrices by 96 parts each took 103 us; it is bound by
-// memory only once a few thousand workgroups are in flight.
-int group_nparts(int64_t m, int64_t n) { return (int)std::min<int64_t>(m, std::max<int64_t>(1, m * n / 8192)); }
+// Norm partials per problem: one for about 1024 chunks of eight elements. A pass
+// over three 6144 x 2048 matrices by 96 parts each took 103 us, by 1536 41; it is
+// bound by memory only once a few thousand workgroups are in flight.
+int group_nparts(int64_t m, int64_t n)
+{
+    const int64_t chunks = std::max(ceil_div(m, 8) * n, m * ceil_div(n, 8));
+    return (int)std::min<int64_t>(1 << 20, std::max<int64_t>(1, chunks / 1024));
+}
 
 // Tiles are Th x Tw (square: Th = Tw = T; rectangular tiles are the
 // tile-shape study's); Th = Tw = 0 stands for T = infinity. A matrix is one
