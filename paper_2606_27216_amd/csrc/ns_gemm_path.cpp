@@ -135,18 +135,24 @@ int plan_groups(int64_t n_mats, const int64_t* rows, const int64_t* cols, int Th
 
 // Takes the groups that the block products (ns_block_gemm.hip) serve: 16-bit
 // operands, c != 0 (their B' = alpha (A A + (beta / alpha) A) + a I divides by
-// alpha), row offsets inside 32 bits, and iterates that at most double when
-// rounded up to multiples of 64. Measured against the tuned library products
+// alpha = c / s^4, which has to stay a normal number), and iterates that at most
+// double when rounded up to multiples of 64. Measured against the tuned library products
 // (us a call, K = 5, 2048 x 2048 cut into Th x Tw): 64 x 64 186 / 261, 96 x 96
 // 186 / 290, 128 x 128 130 / 204, 192 x 192 144 / 394, 256 x 256 128 / 263,
 // 128 x 512 93 / 197; whole 100 x 3000 128 / 205, 200 x 200 77 / 478. Below 64
-// rows most of a tile would be padding, so those stay with the library.
+// rows most of a tile would be padding, so those stay with the library. So do
+// long iterates of few rows: GRAM has few tiles and walks each one's n / 32
+// slices in turn, 0.12 us a slice, where the library splits k (one whole matrix,
+// own / library: 64 x 4096 136 / 169, 64 x 8192 218 / 169, 64 x 50000 1032 / 333,
+// 256 x 8192 248 / 208, 512 x 16384 435 / 312, 1024 x 16384 559 / 572,
+// 2048 x 32768 2667 / 3285, 2048 x 65536 5738 / 5553): the line is at n = 4096,
+// from 1024 rows on at n = 32768.
 void choose_route(std::vector<Group>& groups, GemmOperand op, float b, float c)
 {
     for (Group& g : groups) {
         const int64_t m = ceil_div(g.m0, 64) * 64, n = ceil_div(g.n0, 64) * 64;
-        g.own = op != GemmOperand::F32 && c != 0.f && fabs((double)b / (double)c) < 1e20 && n <= (1 << 22) &&
-                m * (m + n) <= 2 * (int64_t)g.m0 * ((int64_t)g.m0 + g.n0);
+        g.own = op != GemmOperand::F32 && fabs((double)c) > 1e-20 && fabs((double)b / (double)c) < 1e20 &&
+                n <= (m >= 1024 ? 32768 : 4096) && m * (m + n) <= 2 * (int64_t)g.m0 * ((int64_t)g.m0 + g.n0);
         if (!g.own) continue;
         g.m = (int)m;
         g.n = (int)n;
