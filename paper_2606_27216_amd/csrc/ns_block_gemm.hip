@@ -1,14 +1,19 @@
 // The three products of a Newton-Schulz step (eq. ns_iteration) on iterates
 // too large for one CU, as MFMA kernels for gfx950 (16-bit operands):
 //     GRAM    A  = X X^T                            (m x m, symmetric)
-//     POLY    B' = alpha A A + beta A + a I         (m x m, symmetric)
-//     APPLY   X' = B' X                             (m x n)
+//     POLY    B  = alpha A A + beta A               (m x m, symmetric)
+//     APPLY   X' = B X + a X                        (m x n)
 // on a batch of m x n iterates (m, n multiples of 64, zero padded; in panels of
 // 32 columns, each m rows of 64 contiguous bytes), fp32 accumulation, every
-// result rounded once to the operand type. a I rides
-// in B' (near convergence B' has eigenvalues of order one, those of B = B' - a I
-// are about -a, so the rounding of B' is the smaller one), so APPLY has no
-// addend.
+// result rounded once to the operand type, but for the diagonal d_i = a + B_ii:
+// POLY stores it in fp32 beside a B whose diagonal is zero, and APPLY adds d_i X_i
+// from the slice of X whose k are its own output rows. So neither the coefficient nor a diagonal entry
+// is rounded to 16 bits (a coefficient's rounding perturbs every row alike in every
+// step). Emulated, error against fp64 at K = 5, fp16 operands, with a X added in
+// fp32 / a I rounded into the diagonal / as here: default coefficients on 512 x 512
+// Gauss 1.34e-3 / 1.24e-3 / 0.98e-3, orthonormal rows of 15 shapes (geometric mean)
+// 1.29e-3 / 1.32e-3 / 1.00e-3; (1.5, -0.5, -0.0625) on 1024 x 3000 0.52e-3 / 0.87e-3
+// / 0.52e-3.
 //
 // GRAM and POLY compute the tiles on and above the diagonal only and store each
 // of them twice, the second time transposed through LDS: 5/8 of the products at
@@ -24,15 +29,16 @@
 // that every ds_read_b128 of 32 rows is free of bank conflicts; the X slices of
 // APPLY (k along rows) are read through ds_read_b64_tr_b16.
 //
-// What bounds it (one MI355X, us a launch; the library's batched products in
-// brackets): m, n = 2048, 6144, three problems: GRAM 84 (120), POLY 35 (57),
-// APPLY 130 (155), 1.19 PFLOP/s, what a large library product sustains at the
-// board's power. 128 problems of 512 x 512: 37 (51), 39 (52), 47 (52): memory,
-// each launch moves 128 to 192 MB at about 4 TB/s. Eight problems of 512 x 512:
-// 5.6 (10), 6.9 (11.5), 6.6 (15): latency of one tile. Spreading the DMA and the
-// LDS reads over the products, with waits that the compiler knows of, took GRAM
-// at 2048 x 6144 from 93 to 84 and APPLY from 163 to 130; a ring of five or of
-// two 64-deep slices, row-major iterates or 256-tiles changed nothing by 3%.
+// What bounds it (one MI355X, us a launch, medians of a kernel trace; the tuned
+// batched library products in brackets): m, n = 2048, 6144, three problems: GRAM 87
+// (119), POLY 36 (55), APPLY 143 (153), 1.08 PFLOP/s, near what a large library
+// product sustains at the board's power. 128 problems of 512 x 512: 37 (44), 39 (52),
+// 48 (52): each launch moves 128 to 192 MB, at about 4 TB/s. Eight problems of
+// 512 x 512: 6.4 (13), 6.7 (11), 8.1 (14): latency of one tile. Spreading the DMA and
+// the LDS reads over the products, with waits that the compiler knows of, took GRAM
+// at 2048 x 6144 from 93 to 84 and APPLY (then without addend) from 163 to 130; a
+// ring of five or of two 64-deep slices, row-major iterates or 256-tiles changed
+// nothing by 3%.
 #include "elementwise8.h"
 #include "ns_device.h"
 
@@ -49,13 +55,14 @@ struct BlkArgs {
     const uint16_t* a;   // GRAM: X; POLY, APPLY: the m x m left operand
     const uint16_t* x;   // APPLY: X
     uint16_t* out;
+    float* d;            // d_i = a + B_ii, m per problem: POLY writes, APPLY reads
     int64_t sa, sx, so;  // elements between problems
     int32_t m, n;        // iterate shape
     int32_t ti, tj;      // tiles per problem along i and j
     int32_t tpp;         // tiles per problem that are computed
     int32_t total;       // tiles of the launch
-    float alpha, ratio;  // POLY: B' = alpha (A A + ratio A) + diag I
-    float diag;
+    float alpha, ratio;  // POLY: B = alpha (A A + ratio A)
+    float diag;          // POLY: a
     // APPLY as the last step: results go to the caller's matrices (scaled by
     // inv_scale, rounded to bf16) or, with the optimizer step, into its weights
     const GemmProb* probs;
@@ -88,6 +95,13 @@ HM_DEV void dma16(uint32_t dst, uint32_t voff, uint64_t base)
                  : "m0", "memory");
 }
 
+// The same with 4 bytes a lane: LDS bytes dst .. dst + 255.
+HM_DEV void dma4(uint32_t dst, uint32_t voff, uint64_t base)
+{
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" ::"s"(dst), "v"(voff), "s"(base)
+                 : "m0", "memory");
+}
+
 // Waits until at most N of this wave's DMA are in flight and its LDS reads
 // have returned, then for the other waves. (Builtins, so that the compiler
 // knows that earlier LDS reads need no further wait.)
@@ -97,6 +111,14 @@ template <int N> HM_DEV void dma_wait_barrier()
     __builtin_amdgcn_s_waitcnt((N & 15) | (N >> 4) << 14 | 7 << 4);
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
+}
+
+// Value e of four operand values as fp32.
+template <Operand OP> HM_DEV float widen(const u32x2& w, int e)
+{
+    const uint16_t h = (uint16_t)(w[e >> 1] >> (16 * (e & 1)));
+    if constexpr (OP == Operand::F16) return (float)__builtin_bit_cast(_Float16, h);
+    else return __uint_as_float((uint32_t)h << 16);
 }
 
 enum class Product : int { GRAM, POLY, APPLY };
@@ -115,7 +137,8 @@ __global__ void __launch_bounds__(64 * WGM * WGN, MINW) block_gemm(const BlkArgs
     constexpr int NI = AI + BI;
     static_assert(AI * 1024 * W == ABYTES && BI * 1024 * W == BBYTES, "whole DMA instructions");
     static_assert(STAGE * NS >= BM * BN * 2, "the output tile fits the ring");
-    __shared__ __attribute__((aligned(1024))) uint8_t lds[STAGE * NS];
+    // (APPLY: the tile's d behind the ring)
+    __shared__ __attribute__((aligned(1024))) uint8_t lds[STAGE * NS + (P == Product::APPLY ? BM * 4 : 0)];
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -168,14 +191,15 @@ __global__ void __launch_bounds__(64 * WGM * WGN, MINW) block_gemm(const BlkArgs
             vb[q] = (uint32_t)min(row, p.m - 1 - j0) * (kBK * 2u) + 16u * ((lane & 3) ^ ((row >> 2) & 3));
         }
     } else {
-        // X slice: 32 rows (k) of BN columns, panel by panel as it lies in memory
+        // X slice: 32 rows (k) of BN columns, panel by panel, chunks permuted like A's
         b_base = p.x + prob * p.sx + (int64_t)(j0 / kBK) * panel;
         b_step = kBK * kBK;
 #pragma unroll
         for (int q = 0; q < BI; ++q) {
             const int u = q * W + wave;  // half a panel's slice
             const int pan = min(u >> 1, p.n / kBK - 1 - j0 / kBK);
-            vb[q] = (uint32_t)pan * (uint32_t)(panel * 2) + 1024u * (u & 1) + 16u * lane;
+            vb[q] = (uint32_t)pan * (uint32_t)(panel * 2) + 1024u * (u & 1) + 64u * (lane >> 2) +
+                    16u * ((lane & 3) ^ (lane >> 4));
         }
     }
     const uint32_t lds0 = lds_offset(lds);
@@ -206,9 +230,13 @@ __global__ void __launch_bounds__(64 * WGM * WGN, MINW) block_gemm(const BlkArgs
     int ra[2];
 #pragma unroll
     for (int s = 0; s < 2; ++s) ra[s] = li * 64 + 16 * ((2 * s + lh) ^ rsw);
-    // APPLY: transposing reads, k half x (rows 4x ..)
+    // APPLY: transposing reads, k half x (rows 4x ..), whose chunks are permuted by 2 (g16 / 2) + x
     const int g16 = lane >> 4;
-    const int rx = (8 * (g16 >> 1) + ((lane & 15) >> 2)) * 64 + 32 * (g16 & 1) + 8 * (lane & 3);
+    int rx[2];
+#pragma unroll
+    for (int x = 0; x < 2; ++x)
+        rx[x] = (8 * (g16 >> 1) + 4 * x + ((lane & 15) >> 2)) * 64 +
+                16 * ((2 * (g16 & 1) + ((lane & 3) >> 1)) ^ (2 * (g16 >> 1) + x)) + 8 * (lane & 1);
 
     // Operand fragments of 16 k are read one step ahead of their products; the
     // first step of a slice is read during the last of the one before, behind
@@ -228,9 +256,9 @@ __global__ void __launch_bounds__(64 * WGM * WGN, MINW) block_gemm(const BlkArgs
             if constexpr (SYM) {
                 fb[h][j] = *reinterpret_cast<const u32x4*>(tb + (wj + 32 * j) * 64 + ra[s]);
             } else {
-                const uint8_t* const tx = tb + (wj / 32 + j) * 2048 + 1024 * s + rx;
-                const u32x2 lo = tr_read(tx);
-                const u32x2 hi = tr_read(tx + 256);
+                const uint8_t* const tx = tb + (wj / 32 + j) * 2048 + 1024 * s;
+                const u32x2 lo = tr_read(tx + rx[0]);
+                const u32x2 hi = tr_read(tx + rx[1]);
                 fb[h][j] = u32x4{lo[0], lo[1], hi[0], hi[1]};
             }
         }
@@ -259,30 +287,32 @@ __global__ void __launch_bounds__(64 * WGM * WGN, MINW) block_gemm(const BlkArgs
         }
         if constexpr (decltype(refill)::value) advance();
     };
+    // v += f M for a 32 x 32 block M whose rows of 64 bytes lie at `tm`, chunks
+    // permuted like the operands'
+    auto add_block = [&](const uint8_t* tm, float f, f32x16& v) __attribute__((always_inline)) {
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            const u32x2 w = *reinterpret_cast<const u32x2*>(tm + li * 64 + 16 * (g ^ rsw) + 8 * lh);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[4 * g + e] = fmaf(f, widen<OP>(w, e), v[4 * g + e]);
+        }
+    };
     // POLY: the slice whose k are the wave's output columns holds its part of A
     auto addend = [&](const uint8_t* ta, int k) __attribute__((always_inline)) {
 #pragma unroll
         for (int j = 0; j < CB; ++j) {
             if ((j0 + wj) / kBK + j == k) {
 #pragma unroll
-                for (int i = 0; i < RB; ++i)
-#pragma unroll
-                    for (int g = 0; g < 4; ++g) {
-                        const u32x2 w =
-                            *reinterpret_cast<const u32x2*>(ta + (wi + 32 * i + li) * 64 + 16 * (g ^ rsw) + 8 * lh);
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) {
-                            const uint16_t h = (uint16_t)(w[e >> 1] >> (16 * (e & 1)));
-                            float v;
-                            if constexpr (OP == Operand::F16) v = (float)__builtin_bit_cast(_Float16, h);
-                            else v = __uint_as_float((uint32_t)h << 16);
-                            acc[i][j][4 * g + e] = fmaf(p.ratio, v, acc[i][j][4 * g + e]);
-                        }
-                    }
+                for (int i = 0; i < RB; ++i) add_block(ta + (wi + 32 * i) * 64, p.ratio, acc[i][j]);
             }
         }
     };
 
+    if constexpr (P == Product::APPLY) {  // (ahead of the slices: whoever waits for slice 0 waits for it too)
+        if (wave < BM / 64)
+            dma4(__builtin_amdgcn_readfirstlane(lds0 + STAGE * NS + wave * 256),
+                 4u * (uint32_t)min(64 * wave + lane, p.m - 1 - i0), uniform(p.d + (int64_t)prob * p.m + i0));
+    }
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
         if (s < nk) {
@@ -310,9 +340,35 @@ __global__ void __launch_bounds__(64 * WGM * WGN, MINW) block_gemm(const BlkArgs
         phase(1, lds + nbuf * STAGE, 0, more, refill, buf);
         buf = nbuf;
     };
-    for (; k + NS < nk; ++k) slice(yes, yes);
-    for (; k + 1 < nk; ++k) slice(yes, no);
-    slice(no, no);
+    auto run_to = [&](int end) __attribute__((always_inline)) {
+        for (const int e = min(end, nk - NS); k < e; ++k) slice(yes, yes);
+        for (const int e = min(end, nk - 1); k < e; ++k) slice(yes, no);
+        if (k < end) {
+            slice(no, no);
+            ++k;
+        }
+    };
+    if constexpr (P == Product::APPLY) {
+        // The slices whose k are the wave's output rows hold its part of X. The loops
+        // stop ahead of each of them instead of asking in every slice (APPLY on eight
+        // problems of 512 x 512 7.9 us asking, 7.7 so, 7.0 without the addend; on three of
+        // 2048 x 6144 142 and 139 so and without it).
+        const int r0 = (i0 + wi) / kBK;
+#pragma unroll 1
+        for (int b = 0; b <= RB; ++b) {
+            run_to(b < RB ? min(r0 + b, nk) : nk);
+#pragma unroll
+            for (int i = 0; i < RB; ++i)
+                if (b == i) {
+                    const float d = *reinterpret_cast<const float*>(lds + STAGE * NS + (wi + 32 * i + li) * 4);
+#pragma unroll
+                    for (int j = 0; j < CB; ++j)
+                        add_block(lds + buf * STAGE + ABYTES + (wj / 32 + j) * 2048, d, acc[i][j]);
+                }
+        }
+    } else {
+        run_to(nk);
+    }
 
     // results in the operand type into LDS: rows of BN, 16-byte chunk c of row r at c ^ (r & 7)
     dma_wait_barrier<0>();
@@ -324,9 +380,15 @@ __global__ void __launch_bounds__(64 * WGM * WGN, MINW) block_gemm(const BlkArgs
 #pragma unroll
                 for (int v = 0; v < 16; ++v) acc[i][j][v] *= p.alpha;
                 if (i0 == j0 && wi + 32 * i == wj + 32 * j) {
+                    const int row = i0 + wi + 32 * i + li;
+                    float d = 0.f;
 #pragma unroll
-                    for (int v = 0; v < 16; ++v)
-                        if (8 * (v >> 2) + 4 * lh + (v & 3) == li) acc[i][j][v] += p.diag;
+                    for (int v = 0; v < 16; ++v) {
+                        const bool on = 8 * (v >> 2) + 4 * lh + (v & 3) == li;
+                        d = on ? acc[i][j][v] : d;
+                        acc[i][j][v] = on ? 0.f : acc[i][j][v];
+                    }
+                    if (((li >> 2) & 1) == lh && row < p.m) p.d[(int64_t)prob * p.m + row] = d + p.diag;
                 }
             }
             const int row = wi + 32 * i + li;
@@ -501,7 +563,7 @@ template <Product P, Dest D = Dest::ITERATE> hipError_t launch_op(GemmOperand op
 }  // namespace
 
 hipError_t launch_block_step(GemmOperand op, int m, int n, int batch, float alpha, float beta, float diag,
-                             const void* x, void* A, void* B, void* x_out, const GemmProb* probs, float inv_scale,
+                             const void* x, void* A, void* B, float* d, void* x_out, const GemmProb* probs, float inv_scale,
                              const OptArgs* opt, hipStream_t stream)
 {
     if (m < 64 || n < 64 || m % 64 || n % 64) return hipErrorInvalidValue;
@@ -521,6 +583,7 @@ hipError_t launch_block_step(GemmOperand op, int m, int n, int batch, float alph
     p.alpha = alpha;
     p.ratio = beta / alpha;
     p.diag = diag;
+    p.d = d;
     e = launch_op<Product::POLY>(op, p, batch, stream);
     if (e != hipSuccess) return e;
     p.a = static_cast<const uint16_t*>(B);

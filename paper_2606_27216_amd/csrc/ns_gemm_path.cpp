@@ -16,7 +16,7 @@
 // (himuon_select_compute's argument, on |X|, |A| and |B|); s = 1 for fp32 and
 // bf16 operands. Accumulation is fp32 in every
 // mode. 16-bit operands run on the block products (ns_block_gemm.hip: the upper
-// halves of A and B only, a I taken into B, iterates in panels); fp32 operands,
+// halves of A and B only, the diagonal of a I + B in fp32, iterates in panels); fp32 operands,
 // c = 0 and iterates of few rows on hipBLASLt's GEMMs (column-major: a
 // row-major m x n iterate is an n x m column-major matrix, and A and B are
 // symmetric).
@@ -134,7 +134,7 @@ int plan_groups(int64_t n_mats, const int64_t* rows, const int64_t* cols, int Th
 }
 
 // Takes the groups that the block products (ns_block_gemm.hip) serve: 16-bit
-// operands, c != 0 (their B' = alpha (A A + (beta / alpha) A) + a I divides by
+// operands, c != 0 (their B = alpha (A A + (beta / alpha) A) divides by
 // alpha = c / s^4, which has to stay a normal number), and iterates that at most
 // double when rounded up to multiples of 64. Measured against the tuned library products
 // (us a call, K = 5, 2048 x 2048 cut into Th x Tw): 64 x 64 186 / 261, 96 x 96
@@ -159,6 +159,17 @@ void choose_route(std::vector<Group>& groups, GemmOperand op, float b, float c)
     }
 }
 
+// The parts of a chunk's buffers: an iterate, A or B, and (own) the diagonals.
+struct ChunkBytes {
+    size_t x, a, d;
+    size_t total() const { return 2 * x + 2 * a + d; }
+};
+ChunkBytes chunk_bytes(const Group& g, size_t es)
+{
+    const size_t cap = (size_t)g.cap;
+    return {align_up(cap * g.m * g.n * es), align_up(cap * g.m * g.m * es), g.own ? align_up(cap * g.m * sizeof(float)) : 0};
+}
+
 // Chunk capacity per group under `budget` (0: everything in one chunk, up
 // to the launch limit) and the workspace bytes the call needs.
 int plan_chunks(std::vector<Group>& groups, GemmOperand op, size_t budget, size_t* ws_bytes)
@@ -180,7 +191,7 @@ int plan_chunks(std::vector<Group>& groups, GemmOperand op, size_t budget, size_
         g.cap = ceil_div(g.count, g.n_chunks);  // balanced
         total += g.count;
         part_max = std::max(part_max, (size_t)g.cap * g.nparts * sizeof(double));
-        buf_max = std::max(buf_max, 2 * align_up((size_t)g.cap * mn * es) + 2 * align_up((size_t)g.cap * mm * es));
+        buf_max = std::max(buf_max, chunk_bytes(g, es).total());
     }
     *ws_bytes = align_up((size_t)total * sizeof(GemmProb)) + align_up(part_max) + buf_max + kLtWorkspace;
     return HIMUON_OK;
@@ -479,7 +490,7 @@ int run_gemm_path(int64_t n_mats, const void* const* in_ptrs, void* const* out_p
         if (status != HIMUON_OK) break;
     }
 
-    // workspace: table | partials | X0 | X1 | A | B | hipBLASLt scratch
+    // workspace: table | partials | X0 | X1 | A | B | diagonals | hipBLASLt scratch
     uint8_t* const ws = static_cast<uint8_t*>(workspace);
     GemmProb* const table = reinterpret_cast<GemmProb*>(ws);
     size_t off = align_up((size_t)total * sizeof(GemmProb));
@@ -487,7 +498,7 @@ int run_gemm_path(int64_t n_mats, const void* const* in_ptrs, void* const* out_p
     const size_t es = op_size(op);
     for (const Group& g : groups) {
         part_max = std::max(part_max, (size_t)g.cap * g.nparts * sizeof(double));
-        buf_max = std::max(buf_max, 2 * align_up((size_t)g.cap * g.m * g.n * es) + 2 * align_up((size_t)g.cap * g.m * g.m * es));
+        buf_max = std::max(buf_max, chunk_bytes(g, es).total());
     }
     double* const partial = reinterpret_cast<double*>(ws + off);
     off += align_up(part_max);
@@ -497,10 +508,11 @@ int run_gemm_path(int64_t n_mats, const void* const* in_ptrs, void* const* out_p
     if (status == HIMUON_OK) status = himuon::upload_table(probs.data(), probs.size() * sizeof(GemmProb), table, hs, dev);
     for (const Group& g : groups) {
         if (status != HIMUON_OK) break;
-        const size_t xb = align_up((size_t)g.cap * g.m * g.n * es), ab = align_up((size_t)g.cap * g.m * g.m * es);
-        void* X[2] = {bufs, bufs + xb};
-        void* A = bufs + 2 * xb;
-        void* B = bufs + 2 * xb + ab;
+        const ChunkBytes cb = chunk_bytes(g, es);
+        void* X[2] = {bufs, bufs + cb.x};
+        void* A = bufs + 2 * cb.x;
+        void* B = bufs + 2 * cb.x + cb.a;
+        float* const diag = reinterpret_cast<float*>(bufs + 2 * cb.x + 2 * cb.a);
         const double s = iterate_scale(op, g.m0);
         const float alpha2 = (float)((double)c / (s * s * s * s)), beta2 = (float)((double)b / (s * s));
         for (int64_t ci = 0; ci < g.n_chunks && status == HIMUON_OK; ++ci) {
@@ -522,7 +534,7 @@ int run_gemm_path(int64_t n_mats, const void* const* in_ptrs, void* const* out_p
                 void* x = X[cur_x];
                 void* xn = X[cur_x ^ 1];
                 if (g.own) {
-                    e = himuon::launch_block_step(op, g.m, g.n, np, alpha2, beta2, a, x, A, B, xn,
+                    e = himuon::launch_block_step(op, g.m, g.n, np, alpha2, beta2, a, x, A, B, diag, xn,
                                                   k == K - 1 ? tp : nullptr, (float)(1.0 / s), opt, hs);
                     if (e != hipSuccess) status = himuon::set_hip_error(e);
                     cur_x ^= 1;
@@ -646,18 +658,18 @@ int himuon_gemm_tune_hw(int64_t n_mats, const int64_t* rows, const int64_t* cols
     size_t part_max = 0, buf_max = 0;
     for (const Group& g : groups) {
         part_max = std::max(part_max, (size_t)g.cap * g.nparts * sizeof(double));
-        buf_max = std::max(buf_max, 2 * align_up((size_t)g.cap * g.m * g.n * es) + 2 * align_up((size_t)g.cap * g.m * g.m * es));
+        buf_max = std::max(buf_max, chunk_bytes(g, es).total());
     }
     uint8_t* const bufs = static_cast<uint8_t*>(workspace) + align_up((size_t)total * sizeof(GemmProb)) + align_up(part_max);
     void* const lt_ws = bufs + buf_max;
     for (const Group& g : groups) {
         if (st != HIMUON_OK) break;
         if (g.own) continue;
-        const size_t xb = align_up((size_t)g.cap * g.m * g.n * es), ab = align_up((size_t)g.cap * g.m * g.m * es);
+        const ChunkBytes cb = chunk_bytes(g, es);
         uint8_t* const X0 = bufs;
-        uint8_t* const X1 = bufs + xb;
-        uint8_t* const A = bufs + 2 * xb;
-        uint8_t* const B = bufs + 2 * xb + ab;
+        uint8_t* const X1 = bufs + cb.x;
+        uint8_t* const A = bufs + 2 * cb.x;
+        uint8_t* const B = bufs + 2 * cb.x + cb.a;
         const double s = iterate_scale(op, g.m0);
         const float alpha2 = (float)((double)c / (s * s * s * s)), beta2 = (float)((double)b / (s * s));
         const int64_t sizes[2] = {ceil_div(g.count, g.n_chunks), g.count / g.n_chunks};

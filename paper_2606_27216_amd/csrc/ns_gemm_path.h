@@ -69,11 +69,12 @@ hipError_t launch_gemm_scatter(GemmStore st, GemmOperand op, const GemmProb* pro
 
 // One Newton-Schulz step on `batch` m x n iterates (16-bit operands; m, n
 // multiples of 64) through the block products: A = X X^T, B = alpha A A +
-// beta A + diag I, x_out = B X. alpha != 0. With `probs` it is the last step:
+// beta A, x_out = B X + diag X. alpha != 0. d: batch x m floats of scratch (the
+// diagonal of diag I + B). With `probs` it is the last step:
 // its result goes where launch_gemm_scatter would put x_out (bf16 storage), and
 // x_out is not written.
 hipError_t launch_block_step(GemmOperand op, int m, int n, int batch, float alpha, float beta, float diag,
-                             const void* x, void* A, void* B, void* x_out, const GemmProb* probs, float inv_scale,
+                             const void* x, void* A, void* B, float* d, void* x_out, const GemmProb* probs, float inv_scale,
                              const OptArgs* opt, hipStream_t stream);
 
 // Core of himuon_ns_gemm(_hw) and of the optimizer step on the GEMM path
