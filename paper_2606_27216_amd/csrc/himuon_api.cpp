@@ -342,9 +342,26 @@ MatDesc make_desc(const void* in, void* out, int64_t rows, int64_t cols, int64_t
     return d;
 }
 
-bool whole_tiles(const MatDesc& d, int Th, int Tw)
+int64_t whole_first(int64_t n_mats, const void* const* in_ptrs, void* const* out_ptrs, const int64_t* rows,
+                    const int64_t* cols, const int64_t* ld_in, const int64_t* ld_out, const OptDesc* opt, int T,
+                    int dtype, Operand op, int32_t* order)
 {
-    return d.rows % Th == 0 && d.cols % Tw == 0 && d.flags == (MAT_VEC_IN | MAT_VEC_OUT);
+    int64_t tiles = 0, n = 0;
+    const bool sorted = op == Operand::F16 && T >= kWholeFirstTile;
+    auto whole = [&](int64_t m) {
+        return rows[m] % T == 0 && cols[m] % T == 0 &&
+               make_desc(in_ptrs[m], out_ptrs[m], rows[m], cols[m], ld_in ? ld_in[m] : cols[m],
+                         ld_out ? ld_out[m] : cols[m], 0, T, dtype, opt ? opt[m].mom : nullptr)
+                       .flags == (MAT_VEC_IN | MAT_VEC_OUT);
+    };
+    for (int64_t m = 0; sorted && m < n_mats; ++m) {
+        if (!whole(m)) continue;
+        order[n++] = (int32_t)m;
+        tiles += (rows[m] / T) * (cols[m] / T);
+    }
+    for (int64_t m = 0; m < n_mats; ++m)
+        if (!sorted || !whole(m)) order[n++] = (int32_t)m;
+    return tiles;
 }
 
 KernelArgs make_kernel_args(const MatDesc* descs, int64_t n_mats, int K, float a, float b, float c)
@@ -448,13 +465,17 @@ int run_tiled(int64_t n_mats, const void* const* in_ptrs, void* const* out_ptrs,
 
     // ---- descriptor table
     std::vector<MatDesc> descs((size_t)n_mats);
+    std::vector<OptDesc> opts(opt_host ? (size_t)n_mats : 0);
+    std::vector<int32_t> order((size_t)n_mats);
+    const int64_t whole = whole_first(n_mats, in_ptrs, out_ptrs, rows, cols, ld_in, ld_out, opt_host, T, dtype, opnd,
+                                      order.data());
     int64_t next = 0;
-    bool whole = true;
-    for (int64_t m = 0; m < n_mats; ++m) {
-        descs[(size_t)m] = make_desc(in_ptrs[m], out_ptrs[m], rows[m], cols[m], ld_in ? ld_in[m] : cols[m],
+    for (int64_t i = 0; i < n_mats; ++i) {
+        const int64_t m = order[(size_t)i];
+        descs[(size_t)i] = make_desc(in_ptrs[m], out_ptrs[m], rows[m], cols[m], ld_in ? ld_in[m] : cols[m],
                                      ld_out ? ld_out[m] : cols[m], next, T, dtype,
                                      opt_host ? opt_host[m].mom : nullptr);
-        whole = whole && whole_tiles(descs[(size_t)m], T, T);
+        if (opt_host) opts[(size_t)i] = opt_host[m];
         next += ceil_div(rows[m], T) * ceil_div(cols[m], T);
     }
 
@@ -472,14 +493,14 @@ int run_tiled(int64_t n_mats, const void* const* in_ptrs, void* const* out_ptrs,
     if (!inl) {
         status = upload_table(descs.data(), descs.size() * sizeof(MatDesc), workspace, hs, dev);
         if (status == HIMUON_OK && opt_host)
-            status = upload_table(opt_host, (size_t)n_mats * sizeof(OptDesc), otab, hs, dev);
+            status = upload_table(opts.data(), opts.size() * sizeof(OptDesc), otab, hs, dev);
     }
     if (status == HIMUON_OK) {
         KernelArgs ka = make_kernel_args(static_cast<const MatDesc*>(workspace), n_mats, K, a, b, c);
         ka.odescs = otab;
         ka.step = opt_host ? 1 : 0;
-        ka.whole_tiles = whole ? 1 : 0;
-        if (inl) set_inline_tables(ka, descs.data(), opt_host, n_mats);
+        ka.whole_tiles = whole;
+        if (inl) set_inline_tables(ka, descs.data(), opt_host ? opts.data() : nullptr, n_mats);
         ka.beta = beta;
         ka.decay = decay;
         ka.lr = lr;

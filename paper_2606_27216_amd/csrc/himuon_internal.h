@@ -62,7 +62,9 @@ struct KernelArgs {
     int32_t nesterov;
     int64_t tile_begin;
     int64_t tile_end;
-    int32_t whole_tiles;  // 1: no tile of the call is cut by its matrix, and all rows are 16-byte aligned
+    // Tiles [0, whole_tiles) of the call belong to matrices that cut none of their
+    // tiles and whose rows are 16-byte aligned (whole_first; 0 where it is not used).
+    int64_t whole_tiles;
     int32_t n_mats;
     int32_t K;
     float a, b, c;
@@ -120,8 +122,14 @@ int plan_tiled_chunks(int64_t n_mats, const int64_t* rows, const int64_t* cols, 
                       size_t chunk_budget_bytes, int64_t* total, int64_t* n_chunks);
 MatDesc make_desc(const void* in, void* out, int64_t rows, int64_t cols, int64_t ld_in, int64_t ld_out,
                   int64_t tile_begin, int Tw, int dtype, const void* mom);
-// True when every tile of the matrix is whole and its rows are aligned, in and out.
-bool whole_tiles(const MatDesc& d, int Th, int Tw);
+// The order in which a call numbers its matrices' tiles: as given, but for fp16
+// operands from T = kWholeFirstTile on those whose tiles are all whole and whose rows are
+// aligned (in, out, momentum) come first. Writes the matrix indices to
+// order[0 .. n_mats) and returns the number of tiles of those first ones.
+constexpr int kWholeFirstTile = 128;
+int64_t whole_first(int64_t n_mats, const void* const* in_ptrs, void* const* out_ptrs, const int64_t* rows,
+                    const int64_t* cols, const int64_t* ld_in, const int64_t* ld_out, const OptDesc* opt, int T,
+                    int dtype, Operand op, int32_t* order);
 KernelArgs make_kernel_args(const MatDesc* descs, int64_t n_mats, int K, float a, float b, float c);
 // Copies the tables of a call of at most kInlineMats matrices into the
 // arguments (descs, odescs become null; `opt` may be null).

@@ -145,11 +145,14 @@ template <int T, int RB> struct F16Shape {
 // the staging turns the loaded G and M into the stored new M and the
 // lookahead, and the write-back turns U into the decayed, tau-scaled update
 // of the loaded W. Without OPT the kernel is the map alone.
-// EDGE: tiles may be cut by the matrix or have unaligned rows. A 128-tile call
-// whose tiles are all whole and aligned (KernelArgs::whole_tiles) runs a kernel
-// without that code (see launch_f16): beside it the compiler allots the registers
-// of the main path differently.
-template <int T, int RB, int CMODE, bool OPT, bool EDGE>
+// TILES: WHOLE kernels take no tile that the matrix cuts or whose rows are
+// unaligned, CUT kernels any; a MIXED one has both tile loops and runs first the
+// call's whole tiles (KernelArgs::whole_tiles), then the others (see launch_f16:
+// beside the code for cut tiles the compiler allots the main path's registers
+// differently).
+enum class Tiles : int { WHOLE, CUT, MIXED };
+
+template <int T, int RB, int CMODE, bool OPT, Tiles TILES>
 __global__ void __launch_bounds__((F16Shape<T, RB>::kThreads), (F16Shape<T, RB>::kMinWavesPerEU)) ns_tiled_f16_kernel(const KernelArgs args)
 {
     constexpr Storage ST = Storage::BF16;
@@ -274,7 +277,7 @@ __global__ void __launch_bounds__((F16Shape<T, RB>::kThreads), (F16Shape<T, RB>:
         const uint32_t tr = lt / tc;
         L.row0 = (int64_t)tr * T;
         L.col0 = (int64_t)(lt - tr * tc) * T;
-        if constexpr (EDGE) {
+        if constexpr (TILES != Tiles::WHOLE) {
             const bool full = L.row0 + T <= L.rows && L.col0 + T <= L.cols;
             const int32_t fl = D.flags;  // (read unconditionally: no dependent scalar load)
             L.vin = full & ((fl & MAT_VEC_IN) != 0);
@@ -303,8 +306,12 @@ __global__ void __launch_bounds__((F16Shape<T, RB>::kThreads), (F16Shape<T, RB>:
     // (w = 0, 1): the wave's row blocks, and with them every LDS offset in the
     // K loop, become compile-time constants folded into the LDS instructions.
     const int p0_rt = p0;
-    auto tile_loop = [&](auto wtag) {
+    int64_t local = (int64_t)blockIdx.x * TPW + tslot;
+    int parity = 0;  // alternates the reduction slots between tiles
+    // the tiles from `local` on, up to `end`; EDGE: they may be cut or unaligned
+    auto tile_loop = [&](auto wtag, auto etag, int64_t end) {
     constexpr int WSPEC = decltype(wtag)::value;  // -1: not specialised
+    constexpr bool EDGE = decltype(etag)::value;
     const int p0 = WSPEC >= 0 ? RB * WSPEC : p0_rt;
     u32x4 raw[NI];
     u32x4 rawm[OPT ? NI : 1];  // OPT: the momentum rows of the tile
@@ -480,8 +487,7 @@ __global__ void __launch_bounds__((F16Shape<T, RB>::kThreads), (F16Shape<T, RB>:
         return v;
     };
 
-    int64_t local = (int64_t)blockIdx.x * TPW + tslot;
-    if (local >= n_tiles) return;  // uniform over the waves that share a tile
+    if (local >= end) return;  // uniform over the waves that share a tile
     TileLoc cur;
     locate(local, cur);
     issue_loads(cur);
@@ -491,11 +497,10 @@ __global__ void __launch_bounds__((F16Shape<T, RB>::kThreads), (F16Shape<T, RB>:
     u32x4 outv[NI];
     TileLoc prv = cur;
     bool pending = false;
-    int parity = 0;  // alternates the reduction slots between tiles
 
     for (;;) {
         const int64_t nlocal = local + (int64_t)gridDim.x * TPW;
-        const bool has_next = nlocal < n_tiles;
+        const bool has_next = nlocal < end;
         TileLoc nxt = cur;
         if (has_next) locate(nlocal, nxt);
         step_prologue(cur);
@@ -1448,23 +1453,28 @@ __global__ void __launch_bounds__((F16Shape<T, RB>::kThreads), (F16Shape<T, RB>:
                 for (int i = 0; i < NI; ++i) raw[i] = u32x4{};
             }
         }
+        local = nlocal;
         if (!has_next) break;
         cur = nxt;
-        local = nlocal;
     }
     store_rows(prv, outv);
     };
+    auto run = [&](auto wtag) {
+        if constexpr (TILES == Tiles::MIXED)
+            tile_loop(wtag, std::false_type{}, min(n_tiles, max((int64_t)0, args.whole_tiles - args.tile_begin)));
+        tile_loop(wtag, std::bool_constant<TILES != Tiles::WHOLE>{}, n_tiles);
+    };
     if constexpr (F16Shape<T, RB>::kSym) {
-        if (p0_rt == 0) tile_loop(std::integral_constant<int, 0>{});
-        else tile_loop(std::integral_constant<int, 1>{});
+        if (p0_rt == 0) run(std::integral_constant<int, 0>{});
+        else run(std::integral_constant<int, 1>{});
     } else {
-        tile_loop(std::integral_constant<int, -1>{});
+        run(std::integral_constant<int, -1>{});
     }
 }
 
 constexpr int kMaxDevices = 64;
 
-template <int T, int RB, int CMODE, bool OPT, bool EDGE>
+template <int T, int RB, int CMODE, bool OPT, Tiles TILES>
 hipError_t launch_f16_kernel(const KernelArgs& args, hipStream_t stream)
 {
     constexpr int TPW = F16Shape<T, RB>::TPW;
@@ -1477,7 +1487,7 @@ hipError_t launch_f16_kernel(const KernelArgs& args, hipStream_t stream)
     int cap = resident[dev].load(std::memory_order_relaxed);
     if (cap == 0) {
         int per_cu = 0, cus = 0;
-        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, ns_tiled_f16_kernel<T, RB, CMODE, OPT, EDGE>, NT, 0);
+        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, ns_tiled_f16_kernel<T, RB, CMODE, OPT, TILES>, NT, 0);
         if (e != hipSuccess) return e;
         e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
         if (e != hipSuccess) return e;
@@ -1488,19 +1498,31 @@ hipError_t launch_f16_kernel(const KernelArgs& args, hipStream_t stream)
     if (n <= 0) return hipSuccess;
     const int64_t groups = (n + TPW - 1) / TPW;
     const int grid = (int)(groups < cap ? groups : cap);
-    hipLaunchKernelGGL((ns_tiled_f16_kernel<T, RB, CMODE, OPT, EDGE>), dim3(grid), dim3(NT), 0, stream, args);
+    hipLaunchKernelGGL((ns_tiled_f16_kernel<T, RB, CMODE, OPT, TILES>), dim3(grid), dim3(NT), 0, stream, args);
     return hipGetLastError();
 }
 
+// Which 128- and 256-tile calls run which kernel (us a call, K = 5; before the 16-byte
+// accesses to cut tiles / CUT / WHOLE or MIXED). All tiles whole, T = 128: 12352 tiles
+// c < 0 565 / 575 / 561, c = 0 443 / 455 / 446, 960 tiles c < 0 46.5 / 47.4 / 46.2; a
+// step of 12352 725 / - / 715. T = 256, c > 0, 64 tiles 84.2 / 84.8 / 84.0, larger calls
+// within 0.4% of each other, c = 0 3088 tiles 918 / 923 / 928; T = 64 and T = 32 before
+// and CUT within 0.5%. 128-tiles beside cut
+// ones, step: 960 whole tiles 90.2 / 82.9 / 81.9, 12352 745 / 773 / 723; map, c > 0:
+// 1024 whole tiles 71.5 / 68.6 / 70.5, 4096 201 / 194 / 199, 8192 384 / 381 / 379,
+// 12352 557 / 561 / 555: each workgroup begins twice in a MIXED launch, about 2 us.
+constexpr int64_t kMixedMap = 8192;
+
 template <int T, int RB, int CMODE, bool OPT = false> hipError_t launch_f16(const KernelArgs& args, hipStream_t stream)
 {
-    // (c > 0, the coefficients in use, at T = 128: against the start of the unaligned
-    // accesses its kernel with the edge code ran at 0.976, 0.973 (64 tiles) and 0.996
-    // (step), without it 1.005, 1.015 and 1.046; T = 64 0.999 with and 0.985 without)
-    if constexpr (CMODE == 0 && T == 128) {
-        if (args.whole_tiles) return launch_f16_kernel<T, RB, CMODE, OPT, false>(args, stream);
+    if constexpr (T == 128 || (T == 256 && CMODE == 0)) {
+        if (args.whole_tiles >= args.tile_end) return launch_f16_kernel<T, RB, CMODE, OPT, Tiles::WHOLE>(args, stream);
     }
-    return launch_f16_kernel<T, RB, CMODE, OPT, true>(args, stream);
+    if constexpr (T == 128) {
+        if (args.whole_tiles - args.tile_begin >= (OPT ? 1 : kMixedMap))
+            return launch_f16_kernel<T, RB, CMODE, OPT, Tiles::MIXED>(args, stream);
+    }
+    return launch_f16_kernel<T, RB, CMODE, OPT, Tiles::CUT>(args, stream);
 }
 
 }  // namespace

@@ -96,14 +96,16 @@ extern "C" int himuon_ns_tiled_noalloc(int64_t n_mats, const void* const* in_ptr
     const bool inl = n_mats <= himuon::kInlineMats;
     MatDesc inline_descs[himuon::kInlineMats];
     DescWords words;
+    int32_t order[kMaxMats];
+    const int64_t whole = himuon::whole_first(n_mats, in_ptrs, out_ptrs, rows, cols, ld_in, ld_out, nullptr, T, dtype,
+                                              opnd, order);
     int64_t next = 0;
-    bool whole = true;
     if (inl) {
-        for (int64_t m = 0; m < n_mats; ++m) {
-            inline_descs[m] = himuon::make_desc(in_ptrs[m], out_ptrs[m], rows[m], cols[m],
+        for (int64_t i = 0; i < n_mats; ++i) {
+            const int64_t m = order[i];
+            inline_descs[i] = himuon::make_desc(in_ptrs[m], out_ptrs[m], rows[m], cols[m],
                                                 ld_in ? ld_in[m] : cols[m], ld_out ? ld_out[m] : cols[m], next, T,
                                                 dtype, nullptr);
-            whole = whole && himuon::whole_tiles(inline_descs[m], T, T);
             next += ceil_div(rows[m], T) * ceil_div(cols[m], T);
         }
     }
@@ -111,12 +113,11 @@ extern "C" int himuon_ns_tiled_noalloc(int64_t n_mats, const void* const* in_ptr
         const int n = (int)(n_mats - m0 < kPerUpload ? n_mats - m0 : kPerUpload);
         memset(&words, 0, sizeof(words));
         for (int j = 0; j < n; ++j) {
-            const int64_t m = m0 + j;
+            const int64_t m = order[m0 + j];
             const MatDesc d = himuon::make_desc(in_ptrs[m], out_ptrs[m], rows[m], cols[m],
                                                 ld_in ? ld_in[m] : cols[m], ld_out ? ld_out[m] : cols[m], next, T,
                                                 dtype, nullptr);
             memcpy(&words.w[j * kWordsPerDesc], &d, sizeof(MatDesc));
-            whole = whole && himuon::whole_tiles(d, T, T);
             next += ceil_div(rows[m], T) * ceil_div(cols[m], T);
         }
         hipLaunchKernelGGL(upload_descs, dim3(1), dim3(kPerUpload * kWordsPerDesc), 0, hs, words,
@@ -126,7 +127,7 @@ extern "C" int himuon_ns_tiled_noalloc(int64_t n_mats, const void* const* in_ptr
     }
     if (status == HIMUON_OK) {
         himuon::KernelArgs ka = himuon::make_kernel_args(static_cast<const MatDesc*>(table), n_mats, K, a, b, c);
-        ka.whole_tiles = whole ? 1 : 0;
+        ka.whole_tiles = whole;
         if (inl) himuon::set_inline_tables(ka, inline_descs, nullptr, n_mats);
         status = himuon::launch_chunks(T, st, opnd, ka, total, n_chunks, hs);
     }
