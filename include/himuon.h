@@ -186,6 +186,9 @@ int himuon_ns_tiled_hw(int64_t n_mats,
 
 /* Most matrices one himuon_ns_tiled_noalloc call takes. */
 #define HIMUON_NOALLOC_MAX_MATS 1024
+/* Most matrices whose descriptors ride in the kernels' arguments: calls of no
+ * more use no table in device memory, so they may overlap on one GPU. */
+#define HIMUON_INLINE_MATS 32
 
 /*
  * himuon_ns_tiled for callers that cannot allocate memory or own a workspace:
@@ -196,7 +199,7 @@ int himuon_ns_tiled_hw(int64_t n_mats,
  *     library holds on each GPU it runs on until the process ends, so a call
  *     takes at most HIMUON_NOALLOC_MAX_MATS (1024) matrices; more is
  *     HIMUON_ERR_WORKSPACE, returned before anything is enqueued;
- *   - every call on a GPU of more than 32 matrices rewrites that array
+ *   - every call on a GPU of more than HIMUON_INLINE_MATS matrices rewrites that array
  *     through small upload kernels enqueued on `stream` ahead of the tile
  *     kernels (smaller calls carry the table in the tile kernels' own
  *     arguments), so calls on one stream follow each other safely, but calls

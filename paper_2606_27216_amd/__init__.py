@@ -167,6 +167,7 @@ def himuon_ns_tiled_hw(n_mats, in_ptrs, out_ptrs, rows, cols, ld_in, ld_out, Th,
 
 
 NOALLOC_MAX_MATS = 1024  # HIMUON_NOALLOC_MAX_MATS
+INLINE_MATS = 32  # HIMUON_INLINE_MATS: a call of no more matrices needs no table in memory
 
 
 def himuon_ns_tiled_noalloc(n_mats, in_ptrs, out_ptrs, rows, cols, ld_in, ld_out, T, K, a, b, c,
@@ -453,11 +454,6 @@ def _keep_alive(tensors, stream, dev):
             t.record_stream(stream)
 
 
-# Most matrices whose descriptors a call carries in its kernels' arguments
-# (kInlineMats of himuon_internal.h): such a call needs no table in memory.
-_INLINE_MATS = 32
-
-
 def _columns(*lists):
     """Equally long lists of integers as one int64 array, and the address of each
     list's part: one conversion for all arrays of a call."""
@@ -547,7 +543,7 @@ def ns_tiled(inputs, outputs=None, T=128, K=5, coeffs=QUINTIC, compute=COMPUTE_D
     T, K, compute, budget = int(T), int(K), int(compute), int(chunk_budget_bytes)
     square = Tw is None or Tw == T
     raw = _raw_stream(stream, dev)
-    if workspace is None and square and n <= _INLINE_MATS and \
+    if workspace is None and square and n <= INLINE_MATS and \
             (T in (32, 64, 128) or (T == 256 and code == BF16 and compute in (COMPUTE_DEFAULT, COMPUTE_F16))):
         # a fused kernel with its table in the arguments: no workspace to allocate
         st = lib().himuon_ns_tiled_noalloc(n, *arrays, T, K, a, b, c, code, compute, budget, raw or None)

@@ -2,6 +2,8 @@
 // gfx950 kernel family (ns_tiled_kernels.hip). Not part of the public ABI.
 #pragma once
 
+#include "../../include/himuon.h"
+
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -45,7 +47,7 @@ static_assert(sizeof(OptDesc) == 16, "optimizer descriptor layout");
 // Descriptors a launch carries in its own arguments: a call of at most this
 // many matrices copies no table to the device before its kernels (2.5 KiB of
 // kernel arguments).
-constexpr int kInlineMats = 32;
+constexpr int kInlineMats = HIMUON_INLINE_MATS;
 
 // Kernel arguments of one chunk launch: tiles [tile_begin, tile_end).
 struct KernelArgs {

@@ -375,3 +375,11 @@ def test_gemm_hw_workspace_and_validation():
 ])
 def test_calib_mfma_rejects_bad_arguments_before_any_launch(args):
     assert hm.himuon_calib_mfma(*args) == hm.ERR_INVALID_ARG
+
+
+def test_limits_are_the_headers():
+    """ns_tiled takes the entry point without a workspace up to the library's own
+    limit: above it, overlapping calls would share one table."""
+    src = open(os.path.join(ROOT, "include", "himuon.h")).read()
+    limits = {k: int(v) for k, v in re.findall(r"#define (HIMUON_\w+_MATS) (\d+)", src)}
+    assert limits == {"HIMUON_NOALLOC_MAX_MATS": hm.NOALLOC_MAX_MATS, "HIMUON_INLINE_MATS": hm.INLINE_MATS}
