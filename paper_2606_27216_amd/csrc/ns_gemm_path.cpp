@@ -142,11 +142,16 @@ int plan_groups(int64_t n_mats, const int64_t* rows, const int64_t* cols, int Th
 // 128 x 512 93 / 197; whole 100 x 3000 128 / 205, 200 x 200 77 / 478. Below 64
 // rows most of a tile would be padding, so those stay with the library. So do
 // long iterates of few rows: GRAM has few tiles and walks each one's n / 32
-// slices in turn, 0.12 us a slice, where the library splits k (one whole matrix,
-// own / library: 64 x 4096 136 / 169, 64 x 8192 218 / 169, 64 x 50000 1032 / 333,
-// 256 x 8192 248 / 208, 512 x 16384 435 / 312, 1024 x 16384 559 / 572,
-// 2048 x 32768 2667 / 3285, 2048 x 65536 5738 / 5553): the line is at n = 4096,
-// from 1024 rows on at n = 32768.
+// slices in turn, 0.12 us a slice, where the library splits k. One whole matrix /
+// four / twelve of them, library time over own: 256 x 4096 1.11, 512 x 4096 0.96,
+// 256 x 8192 - / 0.83 / 1.28, 512 x 8192 0.85 / 1.05 / 1.49, 768 x 5120 1.17,
+// 768 x 8192 1.01 / 1.13 / 1.29, 896 x 4864 1.12 / 1.27 / 1.36, 960 x 16384 0.96,
+// 64 x 8192 0.8 / 0.74 / 0.77, 1024 x 8192 1.05, 1024 x 16384 0.98 / 1.08 / 1.31,
+// 1024 x 24576 1.07, 1024 x 32768 0.94, 1152 x 32768 1.07, 1536 x 32768 1.15,
+// 2048 x 32768 0.99. The line is at n = 4096, from 1024 rows on at n = 32768: there
+// a single matrix loses 6% at most and batches gain. It asks for the shape alone
+// and not for the number of problems (batches of 256 rows and more gain up to twice
+// the 4096), so that a matrix has the same bits alone, in any batch and in any chunk.
 void choose_route(std::vector<Group>& groups, GemmOperand op, float b, float c)
 {
     for (Group& g : groups) {
