@@ -73,14 +73,6 @@ struct BlkArgs {
 // where APPLY's results go: the next iterate, the output matrices, the weights
 enum class Dest : int { ITERATE, OUT, WEIGHTS };
 
-HM_DEV u32x2 tr_read(const uint8_t* ptr)
-{
-    typedef short s4 __attribute__((ext_vector_type(4)));
-    typedef __attribute__((address_space(3))) s4* lds_s4p;
-    const s4 v = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4p)(ptr));
-    return __builtin_bit_cast(u32x2, v);
-}
-
 HM_DEV uint32_t lds_offset(const void* p)
 {
     return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const uint8_t*)(p);

@@ -123,6 +123,15 @@ template <Operand OP> HM_DEV u32x4 make_slot(const f32x16& v, int s)
     }
 }
 
+// ds_read_b64_tr_b16: eight bytes per lane, transposed over its 16-lane group (LDS).
+HM_DEV u32x2 tr_read(const uint8_t* ptr)
+{
+    typedef short s4 __attribute__((ext_vector_type(4)));
+    typedef __attribute__((address_space(3))) s4* lds_s4p;
+    const s4 v = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4p)(ptr));
+    return __builtin_bit_cast(u32x2, v);
+}
+
 // acc += A_op * B_op for one slot. Lane l of A_op gives row l%32 of the
 // product, lane l of B_op gives column l%32; both carry the same k values.
 // For fp32 the slot's four k-pairs go to the four chains acc[0..3].

@@ -76,29 +76,6 @@ HM_DEV uint32_t wave_max_u32(uint32_t v)
     return v;
 }
 
-// Four consecutive bf16 elements of row gr (columns gc..gc+3) as two packed
-// words, zero outside the matrix (the zero padding of the tiling operator).
-HM_DEV u32x2 load_bf16x4(const void* base, int64_t gr, int64_t gc, int64_t ld, int64_t rows, int64_t cols, bool vec)
-{
-    const uint16_t* p = static_cast<const uint16_t*>(base) + gr * ld + gc;
-    if (vec) return *reinterpret_cast<const u32x2*>(p);
-    uint32_t h[4] = {0u, 0u, 0u, 0u};
-    if (gr < rows) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-            if (gc + e < cols) h[e] = p[e];
-    }
-    return u32x2{h[0] | (h[1] << 16), h[2] | (h[3] << 16)};
-}
-
-HM_DEV u32x2 tr_read(const uint8_t* ptr)
-{
-    typedef short s4 __attribute__((ext_vector_type(4)));
-    typedef __attribute__((address_space(3))) s4* lds_s4p;
-    const s4 v = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4p)(ptr));
-    return __builtin_bit_cast(u32x2, v);
-}
-
 // Row-major fp16 copy of Z. Bytes per row: an odd multiple of 64 (or 64
 // past an even one), so that the row offset modulo the 256-byte bank space
 // steps by a quarter (64 bytes) between consecutive rows. Within each 64-byte
