@@ -20,7 +20,7 @@
  * arrays, device pointers for matrix data and workspace, and a HIP stream
  * passed as void* (a hipStream_t; NULL is the null stream). No entry point
  * allocates device memory or synchronises the device on the compute path.
- * A fused-kernel call over at most 32 matrices carries its descriptor table
+ * A fused-kernel call over at most HIMUON_INLINE_MATS (32) matrices carries its table
  * in the kernels' own launch arguments. Other calls copy their descriptor
  * tables to the workspace from a ring of pinned host slots (allocated on
  * first use, reused once the copy that last used a slot has completed), so
@@ -304,8 +304,11 @@ int himuon_ns_gemm_hw(int64_t n_mats,
  * library's leading heuristic candidates (up to 8), by timing each on the
  * workspace's buffers on `stream`; later calls on this device use the
  * choice. Results never depend on it beyond the rounding of the GEMMs.
- * Products that run on this library's own kernels (16-bit operands, c != 0,
- * all but narrow problems) have nothing to pick: the call validates and returns.
+ * Products that run on this library's own kernels have nothing to pick: calls of
+ * those alone are validated and return. They are 16-bit operands with |c| > 1e-20
+ * (and |b| < 1e20 |c|) on m x n problems (m <= n) of at most 4096 columns, from
+ * 1024 rows on 32768 (both rounded up to multiples of 64), that at most double when
+ * rounded up so (m (m + n) counted).
  *
  * Arguments as himuon_ns_gemm_workspace_size, plus workspace (at least that
  * many bytes; its contents are overwritten) and stream. Unlike the compute
@@ -449,7 +452,8 @@ void himuon_plan_destroy(himuon_plan_t* plan);
  * would use, i.e. the memory-bounded chunking of cross-layer batches of
  * Sec. 4.4.2 (a batch larger than the memory budget is split into the
  * fewest chunks that fit). Tiles are numbered matrix by matrix, row-major over each
- * matrix's R x C grid. The chunk count is the fewest whose per-chunk bytes
+ * matrix's R x C grid (himuon_ns_tiled may take the matrices of a call in another
+ * order, which changes which tiles share a launch and nothing else). The chunk count is the fewest whose per-chunk bytes
  * (2*T*T*sizeof(dtype) per tile) fit chunk_budget_bytes (0: one chunk), and
  * the chunks are balanced: chunk i covers [bounds[i], bounds[i+1]) with
  * sizes that differ by at most one tile.

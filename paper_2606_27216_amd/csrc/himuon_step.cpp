@@ -14,9 +14,9 @@
 //     place on that buffer, and an element-wise epilogue (decay and update);
 //     matrices are taken in consecutive groups whose buffers fit the chunk
 //     budget;
-//   - otherwise (T = 0, large tiles such as 512): the library-GEMM path with
-//     the momentum fused into its norm and gather kernels and the update into
-//     its scatter kernel.
+//   - otherwise (T = 0, large tiles such as 512): the GEMM path with the momentum
+//     fused into its norm and gather kernels and the update into the last block
+//     product or, where the GEMM library's products serve, the scatter kernel.
 #include "himuon_internal.h"
 #include "ns_gemm_path.h"
 #include "optim_kernels.h"

@@ -1,9 +1,11 @@
-// Gather, normalisation and scatter kernels of the library-GEMM path
-// (whole matrices and large tiles). The Newton-Schulz steps themselves are
-// three library GEMMs per step (see ns_gemm_path.cpp); these kernels move a
-// problem's block between the caller's matrix and the iterate buffer:
+// Gather, normalisation and scatter kernels of whole matrices and large tiles
+// (the GEMM path). The Newton-Schulz steps themselves are three products each,
+// the block products (ns_block_gemm.hip) or the GEMM library's (ns_gemm_path.cpp);
+// these kernels move a problem's block between the caller's matrix and the iterate
+// buffer (the last block product scatters its own result):
 //   - B_T (Sec. 2.1, eq. tiling_operator): the block at the top left of an
-//     m x n iterate, zero elsewhere; a whole matrix with more rows than
+//     m x n iterate, zero elsewhere, row-major or (block products) in panels of 32
+//     columns; a whole matrix with more rows than
 //     columns is taken transposed (Phi_K(S^T) = Phi_K(S)^T), so the Gram
 //     matrix is the smaller one;
 //   - the normalisation X0 = S / ||S||_F of Phi_K (Sec. 2.2, eq. phi_k_def;

@@ -1,25 +1,24 @@
-// The library-GEMM path: Phi_K of whole matrices (T = 0, the full-matrix
+// The GEMM path: Phi_K of whole matrices (T = 0, the full-matrix
 // branch, Sec. 4.4.3) and of large tiles (T >= 1, e.g. 512, which cannot
 // stay on one CU; Sec. 4.4.1's multi-kernel path), batched over problems of
 // equal shape (Sec. 4.4.2).
 //
 // A problem is an h x w block worked on as an m x n iterate with m <= n
-// (ns_gemm_path.h). Per step of eq. (ns_iteration), on a batch of iterates
-// stored row-major with stride m*n:
-//     A = X X^T                       (m x m, one GEMM)
-//     B = (c / s^4) A A + (b / s^2) A (one GEMM, C = A)
-//     X <- B X + a X                  (one GEMM, C = X)
+// (ns_gemm_path.h). Per step of eq. (ns_iteration), on a batch of iterates with
+// stride m*n:
+//     A = X X^T                       (m x m, one product)
+//     B = (c / s^4) A A + (b / s^2) A (one product; the library's: C = A)
+//     X <- B X + a X                  (one product; the library's: C = X)
 // X is the rescaled iterate s * X_true: s^2 = min(m, 4096) for fp16 operands,
 // which lifts the O(1/sqrt(mn)) entries of X off fp16's subnormal range and
 // keeps X, A = s^2 A_true and B = b A_true + c A_true^2 inside its range for
 // every m when the scalar iterates stay below the bound checked at planning
 // (himuon_select_compute's argument, on |X|, |A| and |B|); s = 1 for fp32 and
-// bf16 operands. Accumulation is fp32 in every
-// mode. 16-bit operands run on the block products (ns_block_gemm.hip: the upper
-// halves of A and B only, the diagonal of a I + B in fp32, iterates in panels); fp32 operands,
-// c = 0 and iterates of few rows on hipBLASLt's GEMMs (column-major: a
-// row-major m x n iterate is an n x m column-major matrix, and A and B are
-// symmetric).
+// bf16 operands. Accumulation is fp32 in every mode. 16-bit operands run on the
+// block products (ns_block_gemm.hip: the upper halves of A and B only, the diagonal
+// of a I + B in fp32, iterates in panels); fp32 operands, c = 0, iterates of few
+// rows and long ones (choose_route) on hipBLASLt's GEMMs (iterates row-major, which
+// is an n x m column-major matrix; A and B are symmetric).
 #include "ns_gemm_path.h"
 #include "himuon_internal.h"
 #include "../../include/himuon.h"
@@ -224,6 +223,7 @@ int resolve_operand(int dtype, int compute, int K, float a, float b, float c, in
         return HIMUON_OK;
     }
     // |X| <= M, so |s X| <= M s, |s^2 A| <= M^2 s^2 and |B| <= |b| M^2 + |c| M^4
+    // (a is no part of an operand: the block products keep a + B_ii in fp32)
     // (M from the sampled scalar iterates, K + 1 of them: the output is an
     // operand-typed iterate too; 1.25 covers what falls between samples)
     const double M = 1.25 * himuon::iterate_bound(K + 1, a, b, c);

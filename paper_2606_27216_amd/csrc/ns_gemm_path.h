@@ -1,6 +1,7 @@
-// Internal contract of the library-GEMM path (whole matrices, T = 0, and
-// large tiles such as T = 512): the per-problem descriptor the gather and
-// scatter kernels read, and their launchers. Not part of the public ABI.
+// Internal contract of the GEMM path (whole matrices, T = 0, and large tiles
+// such as T = 512): the per-problem descriptor that the gather and scatter
+// kernels and the last block product read, and the launchers. Not part of the
+// public ABI.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -51,19 +52,21 @@ struct OptArgs {
 enum class GemmStore : int { F32 = 0, BF16 = 1 };
 enum class GemmOperand : int { F32 = 1, F16 = 2, BF16 = 3 };
 
-// Partial sums of squares, fp64: part j of problem p covers a fixed slice
-// of its h x w block; result at partial[p * nparts + j].
+// Partial sums of squares, fp64: part j of problem p covers a fixed run of the
+// 8-column chunks of its h x w block; result at partial[p * nparts + j].
 hipError_t launch_gemm_norm_partials(GemmStore st, const GemmProb* probs, int nprob, int nparts,
                                      double* partial, const OptArgs* opt, hipStream_t stream);
 
 // X0 = scale * B / ||B||_F (zero when the block is zero) as the m x n
-// row-major iterate of each problem, stride m * n elements.
+// iterate of each problem, stride m * n elements: row-major, or with `panels` in
+// panels of 32 columns, each m rows of 32 consecutive elements (n a multiple of 32),
+// the layout of the block products.
 hipError_t launch_gemm_gather(GemmStore st, GemmOperand op, const GemmProb* probs, int nprob, int m, int n, int panels,
                               int nparts, const double* partial, double scale, void* x, const OptArgs* opt,
                               hipStream_t stream);
 
-// Output block = inv_scale * (the block's part of the iterate), rounded to
-// the storage type (nearest even for bf16).
+// Output block = inv_scale * (the block's part of the iterate, `panels` as above),
+// rounded to the storage type (nearest even for bf16).
 hipError_t launch_gemm_scatter(GemmStore st, GemmOperand op, const GemmProb* probs, int nprob, int m, int n, int panels,
                                float inv_scale, const void* x, const OptArgs* opt, hipStream_t stream);
 

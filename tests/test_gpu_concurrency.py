@@ -2,9 +2,11 @@
 library's shared host state (the pinned staging ring of descriptor tables,
 the per-device GEMM handle and plans, the per-thread error code) must keep
 every call's result identical, bit for bit, to the same call made alone.
-Routes: the fused map (T = 32), the GEMM-path map (T = 64), and the
-optimizer step inside the fused kernel (T = 128) and on the GEMM path
-(T = 512), each thread with its own weights and momenta."""
+Routes: the fused map (T = 32), the GEMM-path map (T = 64: block products for
+the tiles, library products for none), and the optimizer step inside the fused
+kernel (T = 128) and on the GEMM path (T = 512: block products), each thread with
+its own weights and momenta. Calls on the library's products from several threads
+are in test_gpu_library_products.py."""
 import threading
 
 import pytest

@@ -111,8 +111,9 @@ def test_transpose_equivariance():
 
 
 def test_tuned_kernels_match_oracle():
-    """After the GEMM library's candidates are timed and the fastest kept,
-    results still meet the bars (T = 512 tiles and whole matrices)."""
+    """gemm_tune on calls that the block products serve (nothing to pick: it
+    returns) and their results (T = 512 tiles and whole matrices). Calls whose
+    candidates are timed are in test_gpu_library_products.py."""
     announce("gemm tune, then T=512 and T=0 vs oracle, bf16")
     x = rand((700, 900), torch.bfloat16, 17)
     hm.gemm_tune([(700, 900)], 512, hm.BF16, K=5, coeffs=COEF32)

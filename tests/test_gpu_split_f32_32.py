@@ -19,7 +19,7 @@ def test_split_equals_one_wave(coeffs, K):
     g = torch.Generator(device=DEV)
     g.manual_seed(K)
     xs = [torch.randn(h, w, generator=g, device=DEV) for h, w in ((512, 512), (500, 511), (33, 1), (40, 70))]
-    together = hm.ns_tiled(xs, T=32, K=K, coeffs=coeffs)  # 523 tiles
+    together = hm.ns_tiled(xs, T=32, K=K, coeffs=coeffs)  # 520 tiles
     alone = [hm.ns_tiled([x], T=32, K=K, coeffs=coeffs)[0] for x in xs]
     inplace = [x.clone() for x in xs]
     for x in inplace:
