@@ -101,7 +101,7 @@ size_t himuon_ns_tiled_workspace_size(int64_t n_mats);
 /* Device workspace bytes of the himuon_ns_tiled call with these arguments,
  * whatever serves it: himuon_ns_tiled_workspace_size(n_mats) for a fused
  * kernel; for T = 256 with fp32 storage or bf16 operands, which have no fused
- * 256-tile kernel and run as 256 x 256 problems of the library-GEMM path
+ * 256-tile kernel and run as 256 x 256 problems of the GEMM path
  * inside the same call, what himuon_ns_gemm_workspace_size gives for T = 256.
  * Host-only; 0 when the call would be rejected. */
 size_t himuon_ns_tiled_call_workspace_size(int64_t n_mats, const int64_t* rows, const int64_t* cols, int T,
@@ -208,7 +208,7 @@ int himuon_ns_tiled_hw(int64_t n_mats,
  *   - the call allocates nothing, on the host or the device: no hipMalloc,
  *     no pinned staging; the descriptors travel in kernel arguments;
  *   - only calls a fused kernel serves: T = 256 with fp32 storage or bf16
- *     operands (the library-GEMM route, which needs a workspace) is
+ *     operands (the GEMM route, which needs a workspace) is
  *     HIMUON_ERR_UNSUPPORTED.
  */
 int himuon_ns_tiled_noalloc(int64_t n_mats,
@@ -355,7 +355,7 @@ int himuon_gemm_tune_hw(int64_t n_mats, const int64_t* rows, const int64_t* cols
  *                          operands with c <= 0, run an element-wise prologue
  *                          and epilogue around the fused kernel, with the
  *                          lookahead held in `dtype` in the workspace; any
- *                          other T runs the library-GEMM path with the
+ *                          other T runs the GEMM path with the
  *                          momentum fused into its gather and the update into
  *                          its scatter.
  * lr, momentum, weight_decay, nesterov, scale_c   the step's scalars (finite).

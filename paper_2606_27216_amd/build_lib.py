@@ -44,7 +44,7 @@ SOURCES = [
     ("himuon_plan.cpp", []),
     ("calib_mfma.hip", []),
 ]
-# The whole-matrix and large-tile path runs its Newton-Schulz GEMMs on hipBLASLt.
+# The products of whole matrices and large tiles that the block products do not serve run on hipBLASLt.
 LINK_LIBS = ["-lhipblaslt"]
 
 

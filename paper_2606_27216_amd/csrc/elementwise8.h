@@ -1,5 +1,5 @@
 // Eight consecutive elements of a row as fp32, for the memory-bound kernels
-// (gather/scatter of the library-GEMM path and the optimizer-step
+// (gather/scatter of the GEMM path and the optimizer-step
 // prologue/epilogue). `vec` selects one 16-byte access (bf16) or two (fp32);
 // it requires the chunk to be whole (n == 8) and 16-byte aligned. Elements
 // at or beyond n read as zero and are not written.

@@ -451,7 +451,7 @@ int run_tiled(int64_t n_mats, const void* const* in_ptrs, void* const* out_ptrs,
     const Operand opnd = (Operand)op;
     if (!has_kernel(T, st, opnd)) {
         // 256-tiles without a fused kernel (fp32 storage, bf16 operands): each
-        // tile is a 256 x 256 problem of the library-GEMM path, in the same call
+        // tile is a 256 x 256 problem of the GEMM path, in the same call
         if (T == 256 && !opt_host)
             return run_gemm_path(n_mats, in_ptrs, out_ptrs, nullptr, nullptr, rows, cols, ld_in, ld_out, T, T, K, a,
                                  b, c, dtype, op, workspace, workspace_bytes, chunk_budget_bytes, stream, nullptr);

@@ -56,3 +56,15 @@ def test_distance_from_fp64(shape, coeffs, operand):
     bar = ((emulated(x, 5, coeffs, dtype).double() - r).norm() / r.norm()).item()
     print(f"error {got:.3e}, emulated {bar:.3e}", flush=True)
     assert got <= 1.03 * bar, (got, bar)
+
+
+@pytest.mark.parametrize("shape", [(330, 530), (530, 330), (256, 256)])
+def test_no_steps(shape):
+    """K = 0: gather and scatter alone, through the panels: X / ||X||_F rounded to
+    fp16 (11 bits) and bf16 (8 bits), at most 2^-11 and 2^-8 of the value (and, for
+    fp16 subnormals, 2^-25 of the scaled iterate)."""
+    print(f"[gpu-case] block products, no steps, {shape}", flush=True)
+    x = torch.tensor(np.random.default_rng(8).standard_normal(shape), dtype=torch.bfloat16).to(DEV)
+    (y,) = hm.ns_gemm([x], T=0, K=0, coeffs=COEF32)
+    r = x.double() / x.double().norm()
+    assert ((y.double() - r).abs() <= (2.0**-11 + 2.0**-8 + 2.0**-16) * r.abs() + 2.0**-25).all()
